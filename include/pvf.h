@@ -65,7 +65,9 @@ enum {
                                     non-finite feature were left out          */
 };
 
-/* Arithmetic type of the UNet convolutions (FP32 accumulation throughout).
+/* Arithmetic type of the UNet convolutions (FP32 accumulation throughout; the
+ * FP32 convolutions split their operands exactly into BF16 pieces for the
+ * matrix cores).
  * FP32 is the deployed precision of the paper (Section 2, Fig. 1); BF16 and
  * FP16 follow its mixed-precision roadmap (Section 5); FP8 (OCP e4m3) needs
  * calibration scales (pvf_init_fp8). */
@@ -275,7 +277,7 @@ int pvf_launch_count(const pvf_engine *eng);
 const char *pvf_launch_name(const pvf_engine *eng, int i);
 
 /* Kernel that launch i runs, as it appears in a profiler's kernel name
- * (e.g. "conv_mfma_f32<4, 2, 4, 4, 5, 0>", "track_stage"); NULL if out of
+ * (e.g. "conv_mfma_f32<4, 2, 2, 4, 5, 0>", "track_stage"); NULL if out of
  * range.  Owned by the engine; valid until the next pvf_set_launch_variant,
  * pvf_autotune or pvf_set_track_schedule on it. */
 const char *pvf_launch_kernel(const pvf_engine *eng, int i);

@@ -5,16 +5,34 @@
 //   m = (event, position)  rows of the channels-last activation,
 //   n = output channel     (transposed conv: (tap, output channel)),
 //   k = (tap, input channel).
-// A is never materialised: a block stages the (BM + 4) x 16 halo tile of input
-// rows once per 16-channel chunk in LDS and all five taps read it with a row
-// shift.  LDS tiles are unpadded and XOR-swizzled per 16-byte chunk.  The packed weights are [N][taps][Cin], so one 16-byte LDS read gives
-// a lane four consecutive k of its column.
 //
-// MFMA: v_mfma_f32_16x16x4_f32.  For one 16-wide k chunk, lane group g = lane/16
-// supplies k = 4g+s to the s-th of four MFMAs; A and B use the same order, so
-// the four MFMAs add up the whole chunk.  The k order of every output is fixed
-// by the kernel alone (chunk, tap, s), never by the tile's position, so results
-// are bitwise independent of the batch size and of where an event sits in it.
+// FP32 operands on the BF16 matrix instructions: an FP32 value is the exact
+// sum of three BF16 values (8 + 8 + 8 significant bits, each piece the nearest
+// BF16 of what the pieces before it leave), so a product of two FP32 values
+// is nine BF16 products.  Six of them are accumulated in FP32,
+//   hi*hi, hi*mid, mid*hi, mid*mid, hi*lo, lo*hi;
+// the three left out are below 2^-25 of the product, half an ulp of it.
+// v_mfma_f32_16x16x4_f32 runs at 157 TFLOP/s dense, the BF16 form at 2.5
+// PFLOP/s, so six of those are 2.65 times as fast as one FP32 instruction;
+// the accumulator is rounded once per 32 products and instruction instead of
+// once per 4, and the measured error against FP64 is no larger (2-norm of p
+// over the benchmark's batches: 4.1e-7 to 6.9e-7, 5.1e-7 to 7.8e-7 with the
+// FP32 instruction).  Activations stay FP32 in HBM and are split while they are
+// staged; the weights are split once, at set-up.  Bound by the matrix rate at
+// the card's sustained clock: at 1000 events enc3.c2 takes 1.38 ms, 237 TFLOP/s
+// of FP32 work or 1.42 PFLOP/s of BF16 (2.37 ms and 138 TFLOP/s with the FP32
+// instruction, 86% of its peak), the whole network 9.2 ms (15.0 ms).
+//
+// A is never materialised: a block stages the (BM + 4) x 32 halo tile of input
+// rows once per 32-channel chunk in LDS, as three BF16 planes, and all five
+// taps read it with a row shift.
+//
+// MFMA: v_mfma_f32_16x16x32_bf16.  Lane group g = lane/16 supplies channels
+// 8 g .. 8 g + 7 of the chunk, for the weights and the rows alike.  The k
+// order of every output (chunk, tap, product, MFMA) is fixed by the kernel
+// alone, never by the tile's position or shape, so results are bitwise
+// independent of the batch size, of where an event sits in it and of the
+// tile-shape variant.
 //
 // Epilogues (fused, nothing re-read from HBM):
 //   EPI_STORE  bias + LeakyReLU
@@ -35,30 +53,19 @@ namespace pvf {
 namespace {
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
-constexpr int KC = 16;         // input channels per LDS stage = 4 chunks of 16 B
-
-// LDS rows are KC floats (4 chunks of 16 B) with no padding; chunk q of row r
-// is stored at position q ^ swz(r), swz(r) = 2 * bit 3 of r.  Read-pattern
-// probes on gfx950 show that bits 1..2 of r would make every fragment read
-// conflict-free (with this one only the halo reads of tap 0 are), yet the
-// dominant FP32 layer ran slower with it in repeated A/B runs: 6% with the
-// weight rows in (column, tap) order, under 1% with the tap-major rows used
-// now (cause not pinned down).
-__device__ __forceinline__ int swz(int r) { return (r >> 2) & 2; }
-__device__ __forceinline__ int lds_at(int r, int q) { return (r * 4 + (q ^ swz(r))) * 4; }   // in floats
+constexpr int KC = 32;         // input channels per stage
+constexpr int FRAG = 1024;     // bytes of one packed weight fragment: 16 columns x 32 channels of one piece
 
 __device__ __forceinline__ float lrelu(float x, float s) { return x >= 0.f ? x : s * x; }
 
-// Occupancy target handed to the register allocator: as many waves per SIMD
-// as the block's LDS allows on one CU (160 KB), at most 4 (128 registers);
-// none for the register-prefetch variants, which need the registers.
-constexpr int occupancy_target(int lds_bytes, int waves_per_block)
-{
-    const int blocks = lds_bytes > 0 ? 163840 / lds_bytes : 8;
-    const int w = blocks * waves_per_block / 4;
-    return w < 1 ? 1 : (w > 4 ? 4 : w);
-}
+// the products that are accumulated, smallest first: (weight piece, row piece), 0 = hi
+constexpr int kF32Products = 6;
+constexpr int kProd[kF32Products][2] = {{2, 0}, {0, 2}, {1, 1}, {1, 0}, {0, 1}, {0, 0}};
 
 // Epilogue shared by the FP32 kernels, straight from the accumulators.  The
 // kernels issue the MFMA as D^T = W X^T (weight fragment in the A slot), so
@@ -144,220 +151,87 @@ __device__ __forceinline__ void f32_epilogue(const f32x4 (&acc)[TMW][TNW], const
     }
 }
 
-// (register estimate: 4 per accumulator tile and per fragment, about 56
-// others, 40 more for the 4 x 4-tile waves; the target never asks for fewer)
-template <int TMW, int TNW> struct F32Regs {
-    static constexpr int v = 4 * TMW * TNW + 4 * (TMW + TNW) + 56 + (TMW * TNW >= 16 ? 40 : 0);
+// Eight FP32 values as three planes of eight BF16 values; the pieces add up
+// to the value exactly (24 significant bits; below 2^-103 the last piece
+// loses bits to BF16's subnormals).
+__device__ __forceinline__ void split8(const f32x4& x0, const f32x4& x1, u32x4 (&p)[kF32Pieces])
+{
+#pragma unroll
+    for (int h = 0; h < 4; ++h) {
+        f32x2 r = h < 2 ? f32x2{x0[2 * h], x0[2 * h + 1]} : f32x2{x1[2 * h - 4], x1[2 * h - 3]};
+#pragma unroll
+        for (int q = 0; q < kF32Pieces; ++q) {
+            const unsigned u = __builtin_bit_cast(unsigned, __builtin_convertvector(r, bf16x2));
+            p[q][h] = u;
+            if (q + 1 < kF32Pieces) {
+                r[0] -= __builtin_bit_cast(float, u << 16);
+                r[1] -= __builtin_bit_cast(float, u & 0xffff0000u);
+            }
+        }
+    }
+}
+
+// Set-up: weights [n][taps][cin] -> per 32-channel chunk, tap, group of 16
+// columns and piece one 1 KB fragment, in which lane l holds channels
+// 8 (l / 16) .. + 7 of column l % 16.  One thread per lane of a fragment group.
+__global__ __launch_bounds__(256) void split_weights(const float* w, int n, int taps, int cin, uint16_t* pieces)
+{
+    const int t = blockIdx.x * 256 + threadIdx.x;
+    const int lane = t & 63, group = t >> 6;           // group = (chunk * taps + tap) * (n / 16) + column group
+    if (group >= n / 16 * taps * (cin / KC)) return;
+    const int cg = group % (n / 16), step = group / (n / 16);
+    const int tap = step % taps, chunk = step / taps;
+    const f32x4* src = reinterpret_cast<const f32x4*>(w + ((int64_t)(16 * cg + lane % 16) * taps + tap) * cin +
+                                                      KC * chunk + 8 * (lane / 16));
+    u32x4 p[kF32Pieces];
+    split8(src[0], src[1], p);
+#pragma unroll
+    for (int q = 0; q < kF32Pieces; ++q)
+        *reinterpret_cast<u32x4*>(reinterpret_cast<char*>(pieces) + ((int64_t)group * kF32Pieces + q) * FRAG + lane * 16) = p[q];
+}
+
+// LDS rows of a halo plane: at least `rows`, and 2 modulo 8, so that the four
+// planes of a piece start 32 bytes apart modulo 128 and the staging stores of
+// two rows x four planes fall on different banks.
+constexpr int plane_rows(int rows) { return (rows + 5) / 8 * 8 + 2; }
+
+// LDS of a block: XB halo buffers of three pieces x four 8-channel planes
+// (16 bytes per row and plane: the fragment reads of 16 rows are contiguous),
+// and two weight buffers of one (chunk, tap) step each.
+template <int BM, int BN, int XB, int TAPS> struct F32Lds {
+    static constexpr int rows = plane_rows(BM + TAPS - 1);
+    static constexpr int x = kF32Pieces * 4 * rows * 16;
+    static constexpr int w = BN / 16 * kF32Pieces * FRAG;
+    static constexpr int v = XB * x + 2 * w;
 };
-template <int WM, int WN, int TMW, int TNW, int PF, int TAPS>
-struct F32Occ {
-    static constexpr int lds = occupancy_target(4 * KC * (WM * TMW * 16 + TAPS - 1 + WN * TNW * 16 * TAPS), WM * WN);
-    static constexpr int regs = 512 / F32Regs<TMW, TNW>::v;
-    static constexpr int v = PF ? 1 : (lds < regs ? lds : regs);
+// Waves per SIMD handed to the register allocator: what the LDS allows on one
+// CU (160 KB), at most 2 for the 4 x 4-tile waves (64 accumulator and 96
+// fragment registers), 3 for the others.
+template <int WM, int WN, int TMW, int TNW, int XB, int TAPS> struct F32Occ {
+    static constexpr int w = 163840 / F32Lds<WM * TMW * 16, WN * TNW * 16, XB, TAPS>::v * WM * WN / 4;
+    static constexpr int most = TMW * TNW >= 16 ? 2 : 3;
+    static constexpr int v = w < 1 ? 1 : w > most ? most : w;
 };
+
 // FC: enc0.c2 with the first convolution fused into the staging: each halo
 // chunk is computed from five histogram rows (first_conv_at, the operation
 // order of the standalone kernel, so the bits match) instead of read back;
 // guard rows are zero, as in the stored tensor.
-template <int WM, int WN, int TMW, int TNW, int PF, int TAPS, int EPI, bool FC>
+template <int WM, int WN, int TMW, int TNW, int XB, int TAPS, int EPI, bool FC>
 __device__ __forceinline__ void conv_f32_tile(const ConvArgs& a)
 {
-    static_assert(!FC || (TAPS == kTaps && PF == 0), "the fused first convolution feeds a 5-tap, unprefetched tile");
-    constexpr int NT = WM * WN * 64;
+    static_assert(!FC || (TAPS == kTaps && XB == 1), "the fused first convolution feeds a 5-tap, single-buffered tile");
+    constexpr int NW = WM * WN;
+    constexpr int NT = NW * 64;
     constexpr int BM = WM * TMW * 16;
     constexpr int BN = WN * TNW * 16;
     constexpr int RAD = (TAPS - 1) / 2;
     constexpr int XROWS = BM + TAPS - 1;
-    constexpr int XV = XROWS * (KC / 4);          // float4 per stage of the halo tile
-    constexpr int WV = BN * TAPS * (KC / 4);      // float4 per stage of the weight tile
-    constexpr int XPT = (XV + NT - 1) / NT;
-    constexpr int WPT = (WV + NT - 1) / NT;
+    using Lds = F32Lds<BM, BN, XB, TAPS>;
+    constexpr int PLANE = Lds::rows * 16;         // bytes
+    constexpr int WI = Lds::w / FRAG;             // 1 KB loads per weight step
 
-    __shared__ float xs[XROWS * KC];
-    __shared__ float ws[BN * TAPS * KC];
-
-    const int tid = threadIdx.x;
-    const int lane = tid & 63;
-    const int wave = tid >> 6;
-    const int wm = wave % WM;
-    const int wn = wave / WM;
-    const int li = lane & 15;
-    const int lg = lane >> 4;
-
-    // XCD-aware tile order: block b runs on XCD b % 8; every N tile of one M
-    // tile goes to the same XCD back to back, so the halo rows (and the
-    // weights) are served from that XCD's L2 instead of HBM.
-    const int n_tiles = (a.n + BN - 1) / BN;
-    const int m_tiles = (int)((a.m_rows + BM - 1) / BM);
-    const int xcd = (int)(blockIdx.x % kXcds), slot = (int)(blockIdx.x / kXcds);
-    const int m_tile = (slot / n_tiles) * kXcds + xcd;
-    if (m_tile >= m_tiles) return;
-    const int64_t m0 = (int64_t)m_tile * BM;
-    const int n0 = (slot % n_tiles) * BN;
-    const int kw = TAPS * a.cin;
-    const float* in = static_cast<const float*>(a.in);
-    const float* wt = static_cast<const float*>(a.w);
-
-    f32x4 acc[TMW][TNW];
-#pragma unroll
-    for (int i = 0; i < TMW; ++i)
-#pragma unroll
-        for (int j = 0; j < TNW; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-
-    // PF = 1: software pipeline, the next chunk's tiles are fetched into
-    // registers while the current chunk's MFMAs run from LDS.  PF = 0: fetch,
-    // stage and compute in turn (fewer registers, more blocks per CU), every
-    // load of a stage in flight before the first LDS store.
-    // Thread tid owns chunk q = tid % 4 of LDS rows tid / 4 + u * RS in the halo
-    // tile and in the tap-major weight tile (row = tap * BN + column); its
-    // sources are fixed apart from the stage's channel offset.  Halo rows
-    // outside the batch and columns beyond n are clamped to valid ones: they
-    // only feed outputs the epilogue discards.
-    constexpr int RS = NT / 4;
-    constexpr int WROWS = TAPS * BN;
-    static_assert(RS % 16 == 0, "chunk rows of one thread share their swizzle");
-    const int q = tid % 4, row0 = tid / 4;
-    const int lds0 = lds_at(row0, q);             // + u * RS * KC for chunk u
-    auto x_has = [&](int u) __attribute__((always_inline)) { return (u + 1) * RS <= XROWS || row0 + u * RS < XROWS; };
-    auto w_has = [&](int u) __attribute__((always_inline)) { return (u + 1) * RS <= WROWS || row0 + u * RS < WROWS; };
-    const float* xsrc[XPT];
-    const float* wsrc[WPT];
-#pragma unroll
-    for (int u = 0; u < XPT; ++u) {
-        int64_t g = m0 - RAD + min(row0 + u * RS, XROWS - 1);
-        g = g < 0 ? 0 : (g >= a.m_rows ? a.m_rows - 1 : g);
-        xsrc[u] = in + g * a.ld_in + 4 * q;
-    }
-#pragma unroll
-    for (int u = 0; u < WPT; ++u) {
-        const int wr = min(row0 + u * RS, WROWS - 1);
-        const int tap = wr / BN, nn = wr % BN;
-        const int n = n0 + nn < a.n ? n0 + nn : a.n - 1;
-        wsrc[u] = wt + (int64_t)n * kw + tap * a.cin + 4 * q;
-    }
-    f32x4 xr[FC ? 1 : XPT], wr[WPT];
-    auto fetch = [&](int c0) __attribute__((always_inline)) {
-        if constexpr (!FC) {
-#pragma unroll
-            for (int u = 0; u < XPT; ++u) xr[u] = *reinterpret_cast<const f32x4*>(xsrc[u] + c0);
-        }
-#pragma unroll
-        for (int u = 0; u < WPT; ++u) wr[u] = *reinterpret_cast<const f32x4*>(wsrc[u] + c0);
-    };
-    // FC: the halo chunks of stage c0 are computed and stored one at a time,
-    // while the stage's weight loads are in flight.
-    auto stage = [&](int c0) __attribute__((always_inline)) {
-        if constexpr (FC) {
-            const int c = c0 + 4 * q;                 // this thread's 4 channels
-            float fw[4][kTaps], fb[4];
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                fb[v] = a.first_b[c + v];
-#pragma unroll
-                for (int j = 0; j < kTaps; ++j) fw[v][j] = a.first_w[(c + v) * kTaps + j];
-            }
-            const RowMap rmap(m0, a.r_in);
-#pragma unroll
-            for (int u = 0; u < XPT; ++u) {
-                if (!x_has(u)) continue;
-                int64_t g = m0 - RAD + row0 + u * RS;
-                g = g < 0 ? 0 : (g >= a.m_rows ? a.m_rows - 1 : g);
-                int64_t e;
-                int loc;
-                rmap.at((int)(g - m0), e, loc);
-                f32x4 y = {0.f, 0.f, 0.f, 0.f};
-                if (loc >= kGuard && loc < a.r_in - kGuard) {
-                    float x[kTaps];
-#pragma unroll
-                    for (int j = 0; j < kTaps; ++j) x[j] = a.first_x0[g + j - kGuard];
-#pragma unroll
-                    for (int v = 0; v < 4; ++v) y[v] = first_conv_at(fw[v], fb[v], x, a.slope);
-                }
-                *reinterpret_cast<f32x4*>(xs + lds0 + u * RS * KC) = y;
-            }
-        } else {
-#pragma unroll
-            for (int u = 0; u < XPT; ++u)
-                if (x_has(u)) *reinterpret_cast<f32x4*>(xs + lds0 + u * RS * KC) = xr[u];
-        }
-#pragma unroll
-        for (int u = 0; u < WPT; ++u)
-            if (w_has(u)) *reinterpret_cast<f32x4*>(ws + lds0 + u * RS * KC) = wr[u];
-    };
-
-    fetch(0);
-    stage(0);
-    __syncthreads();
-    for (int c0 = 0; c0 < a.cin; c0 += KC) {
-        const bool more = c0 + KC < a.cin;
-        if (PF && more) fetch(c0 + KC);
-#pragma unroll
-        for (int tap = 0; tap < TAPS; ++tap) {
-            f32x4 av[TMW], bv[TNW];
-#pragma unroll
-            for (int i = 0; i < TMW; ++i)
-                av[i] = *reinterpret_cast<const f32x4*>(xs + lds_at(wm * TMW * 16 + i * 16 + li + tap, lg));
-#pragma unroll
-            for (int j = 0; j < TNW; ++j)
-                bv[j] = *reinterpret_cast<const f32x4*>(ws + lds_at(tap * BN + wn * TNW * 16 + j * 16 + li, lg));
-#pragma unroll
-            for (int s = 0; s < 4; ++s)
-#pragma unroll
-                for (int i = 0; i < TMW; ++i)
-#pragma unroll
-                    for (int j = 0; j < TNW; ++j)
-                        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(bv[j][s], av[i][s], acc[i][j], 0, 0, 0);
-        }
-        __syncthreads();
-        if (more) {
-            if (!PF) fetch(c0 + KC);
-            stage(c0 + KC);
-            __syncthreads();
-        }
-    }
-
-    f32_epilogue<WM, TMW, TNW, EPI>(acc, a, m0, n0, tid);
-}
-
-template <int WM, int WN, int TMW, int TNW, int PF, int TAPS, int EPI>
-__global__ __launch_bounds__(WM * WN * 64) __attribute__((amdgpu_waves_per_eu(F32Occ<WM, WN, TMW, TNW, PF, TAPS>::v)))
-void conv_mfma_f32(ConvArgs a)
-{
-    conv_f32_tile<WM, WN, TMW, TNW, PF, TAPS, EPI, false>(a);
-}
-
-// enc0.c2 with the first convolution in its staging (max-pool epilogue); the
-// first convolution's weights take registers, so the occupancy target is two
-// waves per SIMD.
-template <int WM, int WN, int TMW, int TNW>
-__global__ __launch_bounds__(WM * WN * 64) __attribute__((amdgpu_waves_per_eu(2)))
-void conv_mfma_f32_first(ConvArgs a)
-{
-    conv_f32_tile<WM, WN, TMW, TNW, 0, kTaps, EPI_POOL, true>(a);
-}
-
-
-// PF = 2, double-buffered: the next 16-channel stage streams from global
-// memory straight into the second LDS buffer (global_load_lds_dwordx4: lane L
-// fills 16-byte slot L of a 1 KB block = 16 rows of 64 bytes) while the
-// current stage is on the matrix cores, and the fragments of the next tap are
-// read during the current tap's MFMAs.  Rows beyond the batch and columns
-// beyond n are clamped to valid addresses: they only feed outputs the
-// epilogue discards.  Same k order (16-channel chunk, tap, MFMA step).
-template <int WM, int WN, int TMW, int TNW, int TAPS, int EPI>
-__global__ __launch_bounds__(WM * WN * 64) void conv_mfma_f32_db(ConvArgs a)
-{
-    constexpr int NW = WM * WN;
-    constexpr int BM = WM * TMW * 16;
-    constexpr int BN = WN * TNW * 16;
-    constexpr int RAD = (TAPS - 1) / 2;
-    constexpr int ROWB = KC * 4;                     // 64 bytes per LDS row
-    constexpr int XR = (BM + TAPS - 1 + 15) / 16 * 16;
-    constexpr int WRW = BN * TAPS;
-    static_assert(WRW % 16 == 0, "weight rows fill whole 1 KB loads");
-    constexpr int XI = XR / 16, WI = WRW / 16;
-    constexpr int STAGE = (XR + WRW) * KC;           // floats
-    __shared__ __attribute__((aligned(16))) float smem[2 * STAGE];
+    __shared__ __attribute__((aligned(16))) char smem[Lds::v];
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -366,16 +240,20 @@ __global__ __launch_bounds__(WM * WN * 64) void conv_mfma_f32_db(ConvArgs a)
     const int wn = wave / WM;
     const int li = lane & 15;
     const int lg = lane >> 4;
-    const int n_tiles = (a.n + BN - 1) / BN;
-    const int m_tiles = (int)((a.m_rows + BM - 1) / BM);
+
+    // XCD-aware tile order: block b runs on XCD b % 8; every N tile of one M
+    // tile goes to the same XCD back to back, so the halo rows (and the
+    // weights) are served from that XCD's L2 instead of HBM.
+    const int n_tiles = a.n / BN;
+    const int m_tiles = (a.m_rows + BM - 1) / BM;
     const int xcd = (int)(blockIdx.x % kXcds), slot = (int)(blockIdx.x / kXcds);
     const int m_tile = (slot / n_tiles) * kXcds + xcd;
     if (m_tile >= m_tiles) return;
     const int64_t m0 = (int64_t)m_tile * BM;
     const int n0 = (slot % n_tiles) * BN;
-    const int kw = TAPS * a.cin;
     const float* in = static_cast<const float*>(a.in);
-    const float* wt = static_cast<const float*>(a.w);
+    const char* wt = static_cast<const char*>(a.w) + (int64_t)n0 / 16 * kF32Pieces * FRAG + lane * 16;
+    const int64_t wstep = (int64_t)a.n / 16 * kF32Pieces * FRAG;    // bytes of one (chunk, tap) step, all columns
 
     f32x4 acc[TMW][TNW];
 #pragma unroll
@@ -383,117 +261,197 @@ __global__ __launch_bounds__(WM * WN * 64) void conv_mfma_f32_db(ConvArgs a)
 #pragma unroll
         for (int j = 0; j < TNW; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-    // Wave-wide load j fills LDS rows 16 j .. 16 j + 15 of the stage (halo
-    // rows first, then the tap-major weight rows tap * BN + column); this
-    // wave issues j = wave + t * NW, from a per-lane source computed once.
-    constexpr int NJ = XI + WI, JT = (NJ + NW - 1) / NW;
-    const int lrow = lane >> 2, lpos = lane & 3;
-    const float* src[JT];
+    // Halo staging: a thread owns 8 channels (octet tid % 4) of rows tid / 4 +
+    // u * NT / 4.  Rows outside the batch are clamped to valid ones: they only
+    // feed outputs that the epilogue discards.
+    constexpr int RS = NT / 4;
+    constexpr int XPT = (XROWS + RS - 1) / RS;
+    const int oct = tid & 3, row0 = tid >> 2;
+    auto x_has = [&](int u) __attribute__((always_inline)) { return (u + 1) * RS <= XROWS || row0 + u * RS < XROWS; };
+    auto x_row = [&](int u) __attribute__((always_inline)) {
+        const int64_t g = m0 - RAD + row0 + u * RS;
+        return g < 0 ? (int64_t)0 : (g >= a.m_rows ? (int64_t)a.m_rows - 1 : g);
+    };
+    f32x4 xr[FC ? 1 : XPT][2];
+    auto x_fetch = [&](int c0) __attribute__((always_inline)) {
+        if constexpr (!FC) {
 #pragma unroll
-    for (int t = 0; t < JT; ++t) {
-        const int j = min(wave + t * NW, NJ - 1);
-        const bool xj = j < XI;
-        const int row = 16 * (xj ? j : j - XI) + lrow;
-        const int c = lpos ^ swz(row);
-        if (xj) {
-            int64_t gr = m0 - RAD + row;
-            gr = gr < 0 ? 0 : (gr >= a.m_rows ? a.m_rows - 1 : gr);
-            src[t] = in + gr * a.ld_in + 4 * c;
-        } else {
-            const int tap = row / BN, nn = row % BN;
-            const int n = n0 + nn < a.n ? n0 + nn : a.n - 1;
-            src[t] = wt + (int64_t)n * kw + tap * a.cin + 4 * c;
-        }
-    }
-    auto issue = [&](int buf, int c0) __attribute__((always_inline)) {
-        float* base = smem + buf * STAGE;
-#pragma unroll
-        for (int t = 0; t < JT; ++t) {
-            const int j = wave + t * NW;
-            if ((t + 1) * NW <= NJ || j < NJ)
-                __builtin_amdgcn_global_load_lds((const void*)(src[t] + c0),
-                                                 (__attribute__((address_space(3))) void*)(base + 16 * j * KC), 16, 0, 0);
+            for (int u = 0; u < XPT; ++u)
+                if (x_has(u)) {
+                    const f32x4* p = reinterpret_cast<const f32x4*>(in + x_row(u) * a.ld_in + c0 + 8 * oct);
+                    xr[u][0] = p[0];
+                    xr[u][1] = p[1];
+                }
         }
     };
-    (void)ROWB;
+    auto x_put = [&](char* xs, int u, const f32x4& y0, const f32x4& y1) __attribute__((always_inline)) {
+        u32x4 p[kF32Pieces];
+        split8(y0, y1, p);
+#pragma unroll
+        for (int q = 0; q < kF32Pieces; ++q)
+            *reinterpret_cast<u32x4*>(xs + (q * 4 + oct) * PLANE + (row0 + u * RS) * 16) = p[q];
+    };
+    auto x_store = [&](int buf, int c0) __attribute__((always_inline)) {
+        char* xs = smem + buf * Lds::x;
+        if constexpr (FC) {
+            const int c = c0 + 8 * oct;               // this thread's 8 channels
+            const RowMap rmap(m0, a.r_in);
+            float fw[8][kTaps], fb[8];
+#pragma unroll
+            for (int v = 0; v < 8; ++v) {
+                fb[v] = a.first_b[c + v];
+#pragma unroll
+                for (int j = 0; j < kTaps; ++j) fw[v][j] = a.first_w[(c + v) * kTaps + j];
+            }
+#pragma unroll
+            for (int u = 0; u < XPT; ++u) {
+                if (!x_has(u)) continue;
+                const int64_t g = x_row(u);
+                int64_t e;
+                int loc;
+                rmap.at((int)(g - m0), e, loc);
+                f32x4 y[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+                if (loc >= kGuard && loc < a.r_in - kGuard) {
+                    float x[kTaps];
+#pragma unroll
+                    for (int j = 0; j < kTaps; ++j) x[j] = a.first_x0[g + j - kGuard];
+#pragma unroll
+                    for (int v = 0; v < 8; ++v) y[v / 4][v % 4] = first_conv_at(fw[v], fb[v], x, a.slope);
+                }
+                x_put(xs, u, y[0], y[1]);
+            }
+        } else {
+            (void)c0;
+#pragma unroll
+            for (int u = 0; u < XPT; ++u)
+                if (x_has(u)) x_put(xs, u, xr[u][0], xr[u][1]);
+        }
+    };
+    // Weights of step g: WI fragments of 1 KB, contiguous, straight into LDS
+    // in the order the waves read them.
+    auto w_issue = [&](int g) __attribute__((always_inline)) {
+        const char* src = wt + g * wstep;
+        char* dst = smem + XB * Lds::x + (g & 1) * Lds::w;
+#pragma unroll
+        for (int t = 0; t < (WI + NW - 1) / NW; ++t) {
+            const int j = wave + t * NW;
+            if ((t + 1) * NW <= WI || j < WI)
+                __builtin_amdgcn_global_load_lds((const void*)(src + j * FRAG),
+                                                 (__attribute__((address_space(3))) void*)(dst + j * FRAG), 16, 0, 0);
+        }
+    };
 
-    const int nk = a.cin / KC;
-    issue(0, 0);
-    for (int k = 0; k < nk; ++k) {
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        __syncthreads();
-        if (k + 1 < nk) issue((k + 1) & 1, (k + 1) * KC);
-        const float* xs = smem + (k & 1) * STAGE;
-        const float* ws = xs + XR * KC;
-        f32x4 av[2][TMW], bv[2][TNW];
-        auto frag = [&](int tap, int f) {
-#pragma unroll
-            for (int i = 0; i < TMW; ++i)
-                av[f][i] = *reinterpret_cast<const f32x4*>(xs + lds_at(wm * TMW * 16 + i * 16 + li + tap, lg));
-#pragma unroll
-            for (int j = 0; j < TNW; ++j)
-                bv[f][j] = *reinterpret_cast<const f32x4*>(ws + lds_at(tap * BN + wn * TNW * 16 + j * 16 + li, lg));
-        };
-        frag(0, 0);
+    const int nc = a.cin / KC, nk = nc * TAPS;
+    w_issue(0);
+    x_fetch(0);
+    x_store(0, 0);
+    for (int c = 0; c < nc; ++c) {
+        const char* xs = smem + (XB == 2 ? (c & 1) * Lds::x : 0) + lg * PLANE + (wm * TMW * 16 + li) * 16;
 #pragma unroll
         for (int tap = 0; tap < TAPS; ++tap) {
-            if (tap + 1 < TAPS) frag(tap + 1, (tap + 1) & 1);
+            const int g = c * TAPS + tap;
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this wave's part of step g
+            __syncthreads();
+            if (g + 1 < nk) w_issue(g + 1);
+            if (tap == 0 && c + 1 < nc) x_fetch((c + 1) * KC);
+            const char* ws = smem + XB * Lds::x + (g & 1) * Lds::w + wn * TNW * kF32Pieces * FRAG + lane * 16;
+            bf16x8 wf[TNW][kF32Pieces], xf[TMW][kF32Pieces];
 #pragma unroll
-            for (int s = 0; s < 4; ++s)
+            for (int q = 0; q < kF32Pieces; ++q) {
+#pragma unroll
+                for (int j = 0; j < TNW; ++j)
+                    wf[j][q] = *reinterpret_cast<const bf16x8*>(ws + (j * kF32Pieces + q) * FRAG);
+#pragma unroll
+                for (int i = 0; i < TMW; ++i)
+                    xf[i][q] = *reinterpret_cast<const bf16x8*>(xs + q * 4 * PLANE + (i * 16 + tap) * 16);
+            }
+#pragma unroll
+            for (int t = 0; t < kF32Products; ++t)
 #pragma unroll
                 for (int i = 0; i < TMW; ++i)
 #pragma unroll
                     for (int j = 0; j < TNW; ++j)
-                        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(bv[tap & 1][j][s], av[tap & 1][i][s], acc[i][j],
-                                                                          0, 0, 0);
+                        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[j][kProd[t][0]], xf[i][kProd[t][1]],
+                                                                            acc[i][j], 0, 0, 0);
+            if (XB == 2 && tap == TAPS - 1 && c + 1 < nc) x_store((c + 1) & 1, (c + 1) * KC);
+        }
+        if (XB == 1 && c + 1 < nc) {
+            __syncthreads();
+            x_store(0, (c + 1) * KC);
         }
     }
+
     f32_epilogue<WM, TMW, TNW, EPI>(acc, a, m0, n0, tid);
 }
 
-template <int WM, int WN, int TMW, int TNW, int PF, int TAPS, int EPI>
-hipError_t run(const ConvArgs& a, hipStream_t s)
+template <int WM, int WN, int TMW, int TNW, int TAPS, int EPI>
+__global__ __launch_bounds__(WM * WN * 64) __attribute__((amdgpu_waves_per_eu(F32Occ<WM, WN, TMW, TNW, 1, TAPS>::v)))
+void conv_mfma_f32(ConvArgs a)
+{
+    conv_f32_tile<WM, WN, TMW, TNW, 1, TAPS, EPI, false>(a);
+}
+
+// Double-buffered halo: the next chunk is split into the second buffer behind
+// the current chunk's last step, one barrier less per chunk for twice the LDS.
+template <int WM, int WN, int TMW, int TNW, int TAPS, int EPI>
+__global__ __launch_bounds__(WM * WN * 64) __attribute__((amdgpu_waves_per_eu(F32Occ<WM, WN, TMW, TNW, 2, TAPS>::v)))
+void conv_mfma_f32_db(ConvArgs a)
+{
+    conv_f32_tile<WM, WN, TMW, TNW, 2, TAPS, EPI, false>(a);
+}
+
+// enc0.c2 with the first convolution in its staging (max-pool epilogue)
+template <int WM, int WN, int TMW, int TNW>
+__global__ __launch_bounds__(WM * WN * 64) __attribute__((amdgpu_waves_per_eu(F32Occ<WM, WN, TMW, TNW, 1, kTaps>::v)))
+void conv_mfma_f32_first(ConvArgs a)
+{
+    conv_f32_tile<WM, WN, TMW, TNW, 1, kTaps, EPI_POOL, true>(a);
+}
+
+template <int WM, int WN, int TMW, int TNW>
+dim3 tile_grid(const ConvArgs& a)
 {
     constexpr int BM = WM * TMW * 16;
     constexpr int BN = WN * TNW * 16;
     const unsigned m_tiles = (unsigned)((a.m_rows + BM - 1) / BM);
-    const unsigned n_tiles = (unsigned)((a.n + BN - 1) / BN);
-    dim3 grid((m_tiles + kXcds - 1) / kXcds * kXcds * n_tiles);
-    if constexpr (PF == 2)
+    return dim3((m_tiles + kXcds - 1) / kXcds * kXcds * (unsigned)(a.n / BN));
+}
+
+template <int WM, int WN, int TMW, int TNW, int XB, int TAPS, int EPI>
+hipError_t run(const ConvArgs& a, hipStream_t s)
+{
+    const dim3 grid = tile_grid<WM, WN, TMW, TNW>(a);
+    if constexpr (XB == 2)
         hipLaunchKernelGGL((conv_mfma_f32_db<WM, WN, TMW, TNW, TAPS, EPI>), grid, dim3(WM * WN * 64), 0, s, a);
     else
-        hipLaunchKernelGGL((conv_mfma_f32<WM, WN, TMW, TNW, PF, TAPS, EPI>), grid, dim3(WM * WN * 64), 0, s, a);
+        hipLaunchKernelGGL((conv_mfma_f32<WM, WN, TMW, TNW, TAPS, EPI>), grid, dim3(WM * WN * 64), 0, s, a);
     return hipGetLastError();
 }
 
 template <int WM, int WN, int TMW, int TNW>
 hipError_t run_first(const ConvArgs& a, hipStream_t s)
 {
-    constexpr int BM = WM * TMW * 16;
-    constexpr int BN = WN * TNW * 16;
-    const unsigned m_tiles = (unsigned)((a.m_rows + BM - 1) / BM);
-    const unsigned n_tiles = (unsigned)((a.n + BN - 1) / BN);
-    dim3 grid((m_tiles + kXcds - 1) / kXcds * kXcds * n_tiles);
-    hipLaunchKernelGGL((conv_mfma_f32_first<WM, WN, TMW, TNW>), grid, dim3(WM * WN * 64), 0, s, a);
+    hipLaunchKernelGGL((conv_mfma_f32_first<WM, WN, TMW, TNW>), (tile_grid<WM, WN, TMW, TNW>(a)), dim3(WM * WN * 64), 0,
+                       s, a);
     return hipGetLastError();
 }
 
 // Tile-shape variants.  Every variant accumulates each output's k terms in
-// the same order (16-channel chunk, tap, MFMA step), so all of them give
+// the same order (32-channel chunk, tap, product), so all of them give
 // bitwise-identical results; they differ only in speed.
-struct Variant { int wm, wn, tmw, tnw, pf; };
+struct Variant { int wm, wn, tmw, tnw, xb; };
 constexpr Variant kVariants[] = {
-    {4, 1, 4, 2, 0}, {4, 1, 4, 2, 1}, {2, 1, 4, 2, 0},
-    {4, 1, 4, 4, 0}, {4, 1, 4, 4, 1}, {4, 1, 2, 4, 0},
-    {2, 2, 4, 4, 0}, {2, 2, 4, 4, 1}, {4, 2, 4, 4, 0}, {4, 2, 4, 4, 1},
-    {2, 4, 4, 4, 0},
-    {4, 1, 4, 2, 2}, {4, 1, 4, 4, 2}, {4, 2, 4, 4, 2}, {2, 1, 4, 2, 2},   // 11-14: double-buffered
+    {4, 1, 4, 2, 1}, {4, 1, 2, 2, 1}, {2, 1, 4, 2, 1},                      // 0-2: 32 columns
+    {4, 1, 4, 4, 1}, {4, 1, 2, 4, 1}, {2, 1, 4, 4, 1},                      // 3-5: 64 columns
+    {2, 2, 4, 4, 1}, {4, 2, 2, 4, 1}, {4, 2, 4, 4, 1}, {2, 2, 2, 4, 1},     // 6-9: 128 columns
+    {2, 4, 4, 4, 1},                                                        // 10: 256 columns
+    {4, 1, 4, 2, 2}, {4, 1, 4, 4, 2}, {4, 2, 4, 4, 2}, {2, 1, 4, 2, 2},     // 11-14: double-buffered halo
 };
 constexpr int kNumVariants = sizeof(kVariants) / sizeof(kVariants[0]);
 
 #define PVF_VARIANT_CASE(V, TAPS, EPI)                                                                  \
     case V:                                                                                             \
-        return run<kVariants[V].wm, kVariants[V].wn, kVariants[V].tmw, kVariants[V].tnw, kVariants[V].pf, \
+        return run<kVariants[V].wm, kVariants[V].wn, kVariants[V].tmw, kVariants[V].tnw, kVariants[V].xb, \
                    TAPS, EPI>(a, s);
 
 template <int TAPS, int EPI>
@@ -535,6 +493,14 @@ hipError_t dispatch(int v, const ConvArgs& a, hipStream_t s)
 
 }  // namespace
 
+hipError_t launch_split_weights(const float* w, int n, int taps, int cin, uint16_t* pieces, hipStream_t s)
+{
+    if (n % 16 != 0 || cin % KC != 0) return hipErrorInvalidValue;
+    const unsigned threads = (unsigned)(n / 16 * taps * (cin / KC)) * 64;
+    hipLaunchKernelGGL(split_weights, dim3((threads + 255) / 256), dim3(256), 0, s, w, n, taps, cin, pieces);
+    return hipGetLastError();
+}
+
 int f32_variant_count() { return kNumVariants; }
 
 bool f32_variant_ok(int v, int n, int taps, Epi epi)
@@ -548,35 +514,33 @@ bool f32_variant_ok(int v, int n, int taps, Epi epi)
     return bn <= (n < 32 ? 32 : n);
 }
 
-// Defaults from a sweep on MI355X at 1000 events: the 256 x 32 tile with the
-// fewest registers (most blocks per CU) wins every 5-tap layer; the
-// transposed convs prefer wider N tiles.
+// Defaults from a sweep on MI355X (1000 events of the 32-channel network, 123
+// of the 64-channel one): the waves of 32 positions win, as their blocks take
+// half the registers and a third more waves share a CU; 128 columns where
+// there are as many, since a halo tile is then split for twice the columns
+// (enc2.c2 722 us, against 731 with 64 x 64 waves and 724 with 64 columns).
 int f32_default_variant(int n, int cin, int taps, Epi epi)
 {
-    if (epi == EPI_CONVT && taps == 1) return n >= 64 ? 5 : 0;
-    if (epi == EPI_HEAD) return n == 64 ? 3 : 0;
-    if (epi == EPI_STORE && cin >= 128 && n >= 128) return 3;
-    if (n == 64 && cin <= 32) return 5;
-    return 0;
+    (void)cin;
+    (void)taps;
+    if (n == 32) return 1;
+    if (n == 64) return epi == EPI_HEAD ? 3 : 4;
+    return 7;
 }
 
 std::string f32_kernel_name(int v, int taps, Epi epi)
 {
     const Variant& x = kVariants[v];
-    if (x.pf == 2)
-        return "conv_mfma_f32_db<" + std::to_string(x.wm) + ", " + std::to_string(x.wn) + ", " +
-               std::to_string(x.tmw) + ", " + std::to_string(x.tnw) + ", " + std::to_string(taps) + ", " +
-               std::to_string((int)epi) + ">";
-    return "conv_mfma_f32<" + std::to_string(x.wm) + ", " + std::to_string(x.wn) + ", " + std::to_string(x.tmw) +
-           ", " + std::to_string(x.tnw) + ", " + std::to_string(x.pf) + ", " + std::to_string(taps) + ", " +
-           std::to_string((int)epi) + ">";
+    return std::string(x.xb == 2 ? "conv_mfma_f32_db<" : "conv_mfma_f32<") + std::to_string(x.wm) + ", " +
+           std::to_string(x.wn) + ", " + std::to_string(x.tmw) + ", " + std::to_string(x.tnw) + ", " +
+           std::to_string(taps) + ", " + std::to_string((int)epi) + ">";
 }
 
-// Variants that can take the fused first convolution: the single-buffered,
-// unprefetched tiles (their halo staging goes through registers).
+// Variants that can take the fused first convolution: the single-buffered
+// tiles of up to 64 columns (enc0.c2 has 32 or 64).
 bool f32_first_ok(int v)
 {
-    return v == 0 || v == 2 || v == 3 || v == 5;
+    return v >= 0 && v <= 5;
 }
 
 std::string f32_first_kernel_name(int v)
@@ -588,12 +552,14 @@ std::string f32_first_kernel_name(int v)
 
 hipError_t launch_conv_f32_first(const ConvArgs& a, int v, hipStream_t s)
 {
-    if (a.cin % KC != 0 || a.m_rows <= 0 || !f32_first_ok(v) || !f32_variant_ok(v, a.n, kTaps, EPI_POOL))
+    if (a.cin % KC != 0 || a.m_rows <= 0 || a.n % 32 != 0 || !f32_first_ok(v) || !f32_variant_ok(v, a.n, kTaps, EPI_POOL))
         return hipErrorInvalidValue;
     switch (v) {
     case 0: return run_first<kVariants[0].wm, kVariants[0].wn, kVariants[0].tmw, kVariants[0].tnw>(a, s);
+    case 1: return run_first<kVariants[1].wm, kVariants[1].wn, kVariants[1].tmw, kVariants[1].tnw>(a, s);
     case 2: return run_first<kVariants[2].wm, kVariants[2].wn, kVariants[2].tmw, kVariants[2].tnw>(a, s);
     case 3: return run_first<kVariants[3].wm, kVariants[3].wn, kVariants[3].tmw, kVariants[3].tnw>(a, s);
+    case 4: return run_first<kVariants[4].wm, kVariants[4].wn, kVariants[4].tmw, kVariants[4].tnw>(a, s);
     case 5: return run_first<kVariants[5].wm, kVariants[5].wn, kVariants[5].tmw, kVariants[5].tnw>(a, s);
     default: return hipErrorInvalidValue;
     }
@@ -601,7 +567,7 @@ hipError_t launch_conv_f32_first(const ConvArgs& a, int v, hipStream_t s)
 
 hipError_t launch_conv_f32(const ConvArgs& a, int taps, Epi epi, int variant, hipStream_t s)
 {
-    if (a.cin % KC != 0 || a.m_rows <= 0 || !f32_variant_ok(variant, a.n, taps, epi)) return hipErrorInvalidValue;
+    if (a.cin % KC != 0 || a.m_rows <= 0 || a.n % 32 != 0 || !f32_variant_ok(variant, a.n, taps, epi)) return hipErrorInvalidValue;
     if (taps == 5) {
         switch (epi) {
         case EPI_STORE: return dispatch<5, EPI_STORE>(variant, a, s);

@@ -97,7 +97,8 @@ void make_plan(const pvf_spec* s, size_t weight_floats, Plan* p)
     p->weights_bytes = weight_floats * sizeof(float);
     p->weights = take(p->weights_bytes);
     // 16-bit copy of the conv weights, same element offsets as the FP32 layout
-    p->weights_lp = s->compute_dtype == PVF_FP32 ? 0 : take(weight_floats * 2);
+    // (FP32: every weight as three BF16 pieces, at three times those offsets)
+    p->weights_lp = take(weight_floats * 2 * (s->compute_dtype == PVF_FP32 ? kF32Pieces : 1));
     p->mlp_lp = s->compute_dtype == PVF_FP32 ? 0 : take(mlp_lp_elems(kMaxHiddenLayers) * 2);
     p->scales = s->compute_dtype == PVF_FP8_E4M3 ? take(kMaxScaleFloats * sizeof(float)) : 0;
     p->total = layout_work(s, s->max_events, off, p);
@@ -720,7 +721,7 @@ ConvArgs conv_args(pvf_engine* eng, const WeightLayout::Conv& c, const void* in,
     a.cin = c.cin;
     a.m_rows = n_events * rows_per_event;
     a.r_in = rows_per_event;
-    if (eng->spec.compute_dtype == PVF_FP32) a.w = wbase + c.w;
+    if (eng->spec.compute_dtype == PVF_FP32) a.w = at<uint16_t>(eng, eng->plan.weights_lp) + kF32Pieces * c.w;
     else if (eng->spec.compute_dtype == PVF_FP8_E4M3) a.w = at<uint8_t>(eng, eng->plan.weights_lp) + c.w;
     else a.w = at<uint16_t>(eng, eng->plan.weights_lp) + c.w;
     a.bias = wbase + c.b;
@@ -1061,7 +1062,14 @@ static pvf_status init_impl(const pvf_spec* spec, const void* blob, size_t blob_
         if (err == hipSuccess)
             err = hipMemcpyAsync(e->arena + plan.mlp_lp, mlp_fp8.data(), mlp_fp8.size(), hipMemcpyHostToDevice,
                                  e->stream);
-    } else if (err == hipSuccess && spec->compute_dtype != PVF_FP32) {
+    } else if (err == hipSuccess && spec->compute_dtype == PVF_FP32) {
+        // split on the device, from the FP32 weights just uploaded
+        for (const auto& c : e->conv)
+            if (c.variant >= 0 && err == hipSuccess)
+                err = launch_split_weights(reinterpret_cast<const float*>(e->arena + plan.weights) + c.w->w, c.n, c.taps, c.cin,
+                                           reinterpret_cast<uint16_t*>(e->arena + plan.weights_lp) + kF32Pieces * c.w->w,
+                                           e->stream);
+    } else if (err == hipSuccess) {
         pack_weights_lp(e->wl, b.shape, packed, spec->compute_dtype, packed_lp);
         const int dt = spec->compute_dtype;
         pack_mlp<uint16_t>(e, packed, mlp_lp,

@@ -20,6 +20,7 @@ constexpr int kTaps = 5;          // UNet conv kernel size
 constexpr int kGuard = 2;         // zero rows before and after each event
 constexpr int kMaxLevels = 6;
 constexpr size_t kAlign = 256;
+constexpr int kF32Pieces = 3;     // BF16 pieces of an FP32 value on the matrix cores
 constexpr int kXcds = 8;          // MI355X: workgroups go round-robin over 8 XCDs
 
 // Activation layout: channels-last, one block of R = L + 2*kGuard rows per
@@ -41,7 +42,7 @@ struct Plan {
     int units = 1;                 // UNet sequences per event (1, or the interval count)
     Level lv[kMaxLevels];
     size_t weights = 0, weights_bytes = 0;
-    size_t weights_lp = 0;         // 16-bit conv weights (BF16/FP16 engines)
+    size_t weights_lp = 0;         // 16-bit conv weights (FP8: 8-bit; FP32: three BF16 pieces)
     size_t mlp_lp = 0;             // track network packed for the matrix cores (BF16/FP16/FP8 engines)
     // E below is the number of UNet sequences (events x units)
     size_t x0 = 0;                 // [E][R0][1]      scaled histogram (always FP32)
@@ -127,7 +128,7 @@ struct ConvArgs {
     int cin;             // channels read (multiple of 16)
     int m_rows;          // total input rows (= events * R_in)
     int r_in;            // rows per event of the input level
-    const void* w;       // packed [N][taps][cin] (element type = compute dtype)
+    const void* w;       // packed [N][taps][cin] (element type = compute dtype; FP32: fragments of BF16 pieces)
     const float* bias;   // [Cout]
     int n;               // GEMM N (Cout, or 2*Cout for the transposed conv)
     float slope;         // LeakyReLU slope
@@ -286,6 +287,9 @@ std::string conv_kernel_name(int dtype, int variant, int cin, int taps, Epi epi)
 
 // per-precision implementations behind the functions above
 hipError_t launch_conv_f32(const ConvArgs& a, int taps, Epi epi, int variant, hipStream_t s);
+// Set-up: FP32 conv weights w [n][taps][cin] as BF16 pieces, in the order the
+// FP32 tiles read them (3 * n * taps * cin values).
+hipError_t launch_split_weights(const float* w, int n, int taps, int cin, uint16_t* pieces, hipStream_t s);
 int f32_variant_count();
 bool f32_variant_ok(int variant, int n, int taps, Epi epi);
 int f32_default_variant(int n, int cin, int taps, Epi epi);
