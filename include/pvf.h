@@ -276,8 +276,11 @@ int pvf_launch_count(const pvf_engine *eng);
  * of range.  Static storage. */
 const char *pvf_launch_name(const pvf_engine *eng, int i);
 
-/* Kernel that launch i runs, as it appears in a profiler's kernel name
- * (e.g. "conv_mfma_f32<4, 2, 2, 4, 5, 0>", "track_stage"); NULL if out of
+/* Kernel that launch i runs for full batches, as it appears in a profiler's
+ * kernel name (unless a variant was set, by pvf_set_launch_variant or
+ * pvf_autotune, a batch too small to fill the device runs a smaller tile shape
+ * of it, with the same bits;
+ * e.g. "conv_mfma_f32<4, 2, 2, 4, 5, 0>", "track_stage"); NULL if out of
  * range.  Owned by the engine; valid until the next pvf_set_launch_variant,
  * pvf_autotune or pvf_set_track_schedule on it. */
 const char *pvf_launch_kernel(const pvf_engine *eng, int i);

@@ -723,6 +723,9 @@ constexpr Variant kVariants[] = {
     {4, 1, 2, 1, 32, 3},   // 20: head launch with dec0.c1 fused (conv_mfma_fp8x64_dec0, 4 waves, 240 rows)
     {8, 1, 2, 1, 32, 3},   // 21: the same with 8 waves (496 rows)
     {8, 1, 2, 1, 32, 1},   // 22: 512 x 32, 32-channel stages, single-buffered
+    {2, 1, 1, 1, 64, 2},   // 23: 64 x 32 (128 threads)
+    {2, 1, 1, 1, 32, 2},   // 24: 64 x 32, 32-channel stages (128 threads)
+    {2, 1, 2, 1, 64, 2},   // 25: 128 x 32 (128 threads)
 };
 constexpr int kNumVariants = sizeof(kVariants) / sizeof(kVariants[0]);
 
@@ -766,6 +769,9 @@ hipError_t dispatch(int v, const ConvArgs& a, hipStream_t s)
             PVF_FP8_CASE(18)
             PVF_FP8_CASE(19)
             PVF_FP8_CASE(22)
+            PVF_FP8_CASE(23)
+            PVF_FP8_CASE(24)
+            PVF_FP8_CASE(25)
         default: return hipErrorInvalidValue;
         }
     } else if constexpr (TAPS == 1) {
@@ -783,6 +789,8 @@ hipError_t dispatch(int v, const ConvArgs& a, hipStream_t s)
             PVF_FP8_CASE(15)
             PVF_FP8_CASE(16)
             PVF_FP8_CASE(19)
+            PVF_FP8_CASE(23)
+            PVF_FP8_CASE(25)
         default: return hipErrorInvalidValue;
         }
     } else {
@@ -808,6 +816,9 @@ hipError_t dispatch(int v, const ConvArgs& a, hipStream_t s)
             PVF_FP8_CASE(18)
             PVF_FP8_CASE(19)
             PVF_FP8_CASE(22)
+            PVF_FP8_CASE(23)
+            PVF_FP8_CASE(24)
+            PVF_FP8_CASE(25)
         default: return hipErrorInvalidValue;
         }
     }
@@ -849,6 +860,23 @@ int fp8_default_variant(int n, int cin, int taps, Epi epi)
     if (taps == 1) return n >= 256 ? 2 : (n >= 128 ? 3 : 0);
     if (n <= 32) return k64 ? 15 : (epi == EPI_POOL ? 18 : 9);
     return k64 ? 14 : 17;
+}
+
+// Tiles of small batches, from sweeps of 1 to 1000 events of the 32-channel
+// network: 64 x 32 while the device holds all its blocks at once, then 256 x 32
+// until there are eight of them per compute unit (enc3.c2, launch and its
+// event: one event 7.2 us, 11.3 with the default 256 x 64; 35 events 13.1 with
+// 256 x 32, 15.0; 100 events 24.6, 25.4; 200 events 40.4, 38.9).  The fused
+// launches keep their tiles (dec2.c2 with up1, one event: 6.9 us, apart 5.9 and
+// a launch more).
+int fp8_batch_variant(int full, int n, int cin, Epi epi, int m_rows)
+{
+    constexpr int kCus = 256;
+    if (epi == EPI_UP || epi == EPI_HEAD || fp8_first_ok(full)) return full;
+    int v = full;
+    if (tile_blocks(m_rows, n, 64, 32) <= 3 * kCus) v = cin % 64 == 0 ? 23 : 24;
+    else if (epi != EPI_CONVT && tile_blocks(m_rows, n, 256, 32) <= (cin % 64 == 0 ? 8 : 4) * kCus) v = cin % 64 == 0 ? 15 : 18;
+    return fp8_variant_ok(v, n, cin, epi == EPI_CONVT ? 1 : kTaps, epi) ? v : full;
 }
 
 int fp8_default_up_variant(int n, int cin)

@@ -197,18 +197,18 @@ constexpr int plane_rows(int rows) { return (rows + 5) / 8 * 8 + 2; }
 
 // LDS of a block: XB halo buffers of three pieces x four 8-channel planes
 // (16 bytes per row and plane: the fragment reads of 16 rows are contiguous),
-// and two weight buffers of one (chunk, tap) step each.
-template <int BM, int BN, int XB, int TAPS> struct F32Lds {
+// and a ring of D weight buffers of one (chunk, tap) step each.
+template <int BM, int BN, int XB, int D, int TAPS> struct F32Lds {
     static constexpr int rows = plane_rows(BM + TAPS - 1);
     static constexpr int x = kF32Pieces * 4 * rows * 16;
     static constexpr int w = BN / 16 * kF32Pieces * FRAG;
-    static constexpr int v = XB * x + 2 * w;
+    static constexpr int v = XB * x + D * w;
 };
 // Waves per SIMD handed to the register allocator: what the LDS allows on one
 // CU (160 KB), at most 2 for the 4 x 4-tile waves (64 accumulator and 96
 // fragment registers), 3 for the others.
-template <int WM, int WN, int TMW, int TNW, int XB, int TAPS> struct F32Occ {
-    static constexpr int w = 163840 / F32Lds<WM * TMW * 16, WN * TNW * 16, XB, TAPS>::v * WM * WN / 4;
+template <int WM, int WN, int TMW, int TNW, int XB, int D, int TAPS> struct F32Occ {
+    static constexpr int w = 163840 / F32Lds<WM * TMW * 16, WN * TNW * 16, XB, D, TAPS>::v * WM * WN / 4;
     static constexpr int most = TMW * TNW >= 16 ? 2 : 3;
     static constexpr int v = w < 1 ? 1 : w > most ? most : w;
 };
@@ -217,7 +217,7 @@ template <int WM, int WN, int TMW, int TNW, int XB, int TAPS> struct F32Occ {
 // chunk is computed from five histogram rows (first_conv_at, the operation
 // order of the standalone kernel, so the bits match) instead of read back;
 // guard rows are zero, as in the stored tensor.
-template <int WM, int WN, int TMW, int TNW, int XB, int TAPS, int EPI, bool FC>
+template <int WM, int WN, int TMW, int TNW, int XB, int D, int TAPS, int EPI, bool FC>
 __device__ __forceinline__ void conv_f32_tile(const ConvArgs& a)
 {
     static_assert(!FC || (TAPS == kTaps && XB == 1), "the fused first convolution feeds a 5-tap, single-buffered tile");
@@ -227,7 +227,7 @@ __device__ __forceinline__ void conv_f32_tile(const ConvArgs& a)
     constexpr int BN = WN * TNW * 16;
     constexpr int RAD = (TAPS - 1) / 2;
     constexpr int XROWS = BM + TAPS - 1;
-    using Lds = F32Lds<BM, BN, XB, TAPS>;
+    using Lds = F32Lds<BM, BN, XB, D, TAPS>;
     constexpr int PLANE = Lds::rows * 16;         // bytes
     constexpr int WI = Lds::w / FRAG;             // 1 KB loads per weight step
 
@@ -252,7 +252,7 @@ __device__ __forceinline__ void conv_f32_tile(const ConvArgs& a)
     const int64_t m0 = (int64_t)m_tile * BM;
     const int n0 = (slot % n_tiles) * BN;
     const float* in = static_cast<const float*>(a.in);
-    const char* wt = static_cast<const char*>(a.w) + (int64_t)n0 / 16 * kF32Pieces * FRAG + lane * 16;
+    const char* wt = static_cast<const char*>(a.w) + (int64_t)n0 / 16 * kF32Pieces * FRAG;
     const int64_t wstep = (int64_t)a.n / 16 * kF32Pieces * FRAG;    // bytes of one (chunk, tap) step, all columns
 
     f32x4 acc[TMW][TNW];
@@ -269,7 +269,7 @@ __device__ __forceinline__ void conv_f32_tile(const ConvArgs& a)
     const int oct = tid & 3, row0 = tid >> 2;
     auto x_has = [&](int u) __attribute__((always_inline)) { return (u + 1) * RS <= XROWS || row0 + u * RS < XROWS; };
     auto x_row = [&](int u) __attribute__((always_inline)) {
-        const int64_t g = m0 - RAD + row0 + u * RS;
+        const int64_t g = m0 - RAD + min(row0 + u * RS, XROWS - 1);
         return g < 0 ? (int64_t)0 : (g >= a.m_rows ? (int64_t)a.m_rows - 1 : g);
     };
     f32x4 xr[FC ? 1 : XPT][2];
@@ -277,7 +277,7 @@ __device__ __forceinline__ void conv_f32_tile(const ConvArgs& a)
         if constexpr (!FC) {
 #pragma unroll
             for (int u = 0; u < XPT; ++u)
-                if (x_has(u)) {
+                if (D > 2 || x_has(u)) {               // without a branch where the waits are counted
                     const f32x4* p = reinterpret_cast<const f32x4*>(in + x_row(u) * a.ld_in + c0 + 8 * oct);
                     xr[u][0] = p[0];
                     xr[u][1] = p[1];
@@ -329,32 +329,42 @@ __device__ __forceinline__ void conv_f32_tile(const ConvArgs& a)
     };
     // Weights of step g: WI fragments of 1 KB, contiguous, straight into LDS
     // in the order the waves read them.
-    auto w_issue = [&](int g) __attribute__((always_inline)) {
+    auto w_issue = [&](int g, int slot) __attribute__((always_inline)) {
         const char* src = wt + g * wstep;
-        char* dst = smem + XB * Lds::x + (g & 1) * Lds::w;
+        char* dst = smem + XB * Lds::x + slot * Lds::w;
 #pragma unroll
         for (int t = 0; t < (WI + NW - 1) / NW; ++t) {
             const int j = wave + t * NW;
             if ((t + 1) * NW <= WI || j < WI)
-                __builtin_amdgcn_global_load_lds((const void*)(src + j * FRAG),
+                __builtin_amdgcn_global_load_lds((const void*)(src + j * FRAG + lane * 16),
                                                  (__attribute__((address_space(3))) void*)(dst + j * FRAG), 16, 0, 0);
         }
     };
 
     const int nc = a.cin / KC, nk = nc * TAPS;
-    w_issue(0);
+    // The barrier that opens step g: this wave's share of step g has arrived
+    // and its halo stores are done; the loads of steps g + 1 .. g + D - 2, at
+    // least WI / NW each, may still be in flight (halo loads among them, and
+    // the waves that issue one more a step, only make the wait longer).
+    // With D > 2, steps past the last one are issued too, as copies of the
+    // last, so that the count always holds; nothing reads them.
+    auto open = [&]() __attribute__((always_inline)) {
+        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"((D - 2) * (WI / NW)) : "memory");
+    };
+#pragma unroll
+    for (int g = 0; g < D - 1; ++g) w_issue(min(g, nk - 1), g);
     x_fetch(0);
     x_store(0, 0);
+    int ring = 0;                                  // ring slot of step g
     for (int c = 0; c < nc; ++c) {
         const char* xs = smem + (XB == 2 ? (c & 1) * Lds::x : 0) + lg * PLANE + (wm * TMW * 16 + li) * 16;
 #pragma unroll
         for (int tap = 0; tap < TAPS; ++tap) {
             const int g = c * TAPS + tap;
-            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this wave's part of step g
-            __syncthreads();
-            if (g + 1 < nk) w_issue(g + 1);
+            open();
             if (tap == 0 && c + 1 < nc) x_fetch((c + 1) * KC);
-            const char* ws = smem + XB * Lds::x + (g & 1) * Lds::w + wn * TNW * kF32Pieces * FRAG + lane * 16;
+            if (D > 2 || g + 1 < nk) w_issue(min(g + D - 1, nk - 1), ring == 0 ? D - 1 : ring - 1);
+            const char* ws = smem + XB * Lds::x + ring * Lds::w + wn * TNW * kF32Pieces * FRAG + lane * 16;
             bf16x8 wf[TNW][kF32Pieces], xf[TMW][kF32Pieces];
 #pragma unroll
             for (int q = 0; q < kF32Pieces; ++q) {
@@ -374,38 +384,41 @@ __device__ __forceinline__ void conv_f32_tile(const ConvArgs& a)
                         acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[j][kProd[t][0]], xf[i][kProd[t][1]],
                                                                             acc[i][j], 0, 0, 0);
             if (XB == 2 && tap == TAPS - 1 && c + 1 < nc) x_store((c + 1) & 1, (c + 1) * KC);
+            ring = ring + 1 == D ? 0 : ring + 1;
         }
         if (XB == 1 && c + 1 < nc) {
-            __syncthreads();
+            asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");     // every wave has read the chunk
             x_store(0, (c + 1) * KC);
         }
     }
 
+    // no load may reach this block's LDS after the block has ended
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     f32_epilogue<WM, TMW, TNW, EPI>(acc, a, m0, n0, tid);
 }
 
-template <int WM, int WN, int TMW, int TNW, int TAPS, int EPI>
-__global__ __launch_bounds__(WM * WN * 64) __attribute__((amdgpu_waves_per_eu(F32Occ<WM, WN, TMW, TNW, 1, TAPS>::v)))
+template <int WM, int WN, int TMW, int TNW, int D, int TAPS, int EPI>
+__global__ __launch_bounds__(WM * WN * 64) __attribute__((amdgpu_waves_per_eu(F32Occ<WM, WN, TMW, TNW, 1, D, TAPS>::v)))
 void conv_mfma_f32(ConvArgs a)
 {
-    conv_f32_tile<WM, WN, TMW, TNW, 1, TAPS, EPI, false>(a);
+    conv_f32_tile<WM, WN, TMW, TNW, 1, D, TAPS, EPI, false>(a);
 }
 
 // Double-buffered halo: the next chunk is split into the second buffer behind
 // the current chunk's last step, one barrier less per chunk for twice the LDS.
 template <int WM, int WN, int TMW, int TNW, int TAPS, int EPI>
-__global__ __launch_bounds__(WM * WN * 64) __attribute__((amdgpu_waves_per_eu(F32Occ<WM, WN, TMW, TNW, 2, TAPS>::v)))
+__global__ __launch_bounds__(WM * WN * 64) __attribute__((amdgpu_waves_per_eu(F32Occ<WM, WN, TMW, TNW, 2, 2, TAPS>::v)))
 void conv_mfma_f32_db(ConvArgs a)
 {
-    conv_f32_tile<WM, WN, TMW, TNW, 2, TAPS, EPI, false>(a);
+    conv_f32_tile<WM, WN, TMW, TNW, 2, 2, TAPS, EPI, false>(a);
 }
 
 // enc0.c2 with the first convolution in its staging (max-pool epilogue)
-template <int WM, int WN, int TMW, int TNW>
-__global__ __launch_bounds__(WM * WN * 64) __attribute__((amdgpu_waves_per_eu(F32Occ<WM, WN, TMW, TNW, 1, kTaps>::v)))
+template <int WM, int WN, int TMW, int TNW, int D>
+__global__ __launch_bounds__(WM * WN * 64) __attribute__((amdgpu_waves_per_eu(F32Occ<WM, WN, TMW, TNW, 1, D, kTaps>::v)))
 void conv_mfma_f32_first(ConvArgs a)
 {
-    conv_f32_tile<WM, WN, TMW, TNW, 1, kTaps, EPI_POOL, true>(a);
+    conv_f32_tile<WM, WN, TMW, TNW, 1, D, kTaps, EPI_POOL, true>(a);
 }
 
 template <int WM, int WN, int TMW, int TNW>
@@ -417,21 +430,21 @@ dim3 tile_grid(const ConvArgs& a)
     return dim3((m_tiles + kXcds - 1) / kXcds * kXcds * (unsigned)(a.n / BN));
 }
 
-template <int WM, int WN, int TMW, int TNW, int XB, int TAPS, int EPI>
+template <int WM, int WN, int TMW, int TNW, int XB, int D, int TAPS, int EPI>
 hipError_t run(const ConvArgs& a, hipStream_t s)
 {
     const dim3 grid = tile_grid<WM, WN, TMW, TNW>(a);
     if constexpr (XB == 2)
         hipLaunchKernelGGL((conv_mfma_f32_db<WM, WN, TMW, TNW, TAPS, EPI>), grid, dim3(WM * WN * 64), 0, s, a);
     else
-        hipLaunchKernelGGL((conv_mfma_f32<WM, WN, TMW, TNW, TAPS, EPI>), grid, dim3(WM * WN * 64), 0, s, a);
+        hipLaunchKernelGGL((conv_mfma_f32<WM, WN, TMW, TNW, D, TAPS, EPI>), grid, dim3(WM * WN * 64), 0, s, a);
     return hipGetLastError();
 }
 
-template <int WM, int WN, int TMW, int TNW>
+template <int WM, int WN, int TMW, int TNW, int D>
 hipError_t run_first(const ConvArgs& a, hipStream_t s)
 {
-    hipLaunchKernelGGL((conv_mfma_f32_first<WM, WN, TMW, TNW>), (tile_grid<WM, WN, TMW, TNW>(a)), dim3(WM * WN * 64), 0,
+    hipLaunchKernelGGL((conv_mfma_f32_first<WM, WN, TMW, TNW, D>), (tile_grid<WM, WN, TMW, TNW>(a)), dim3(WM * WN * 64), 0,
                        s, a);
     return hipGetLastError();
 }
@@ -439,20 +452,22 @@ hipError_t run_first(const ConvArgs& a, hipStream_t s)
 // Tile-shape variants.  Every variant accumulates each output's k terms in
 // the same order (32-channel chunk, tap, product), so all of them give
 // bitwise-identical results; they differ only in speed.
-struct Variant { int wm, wn, tmw, tnw, xb; };
+struct Variant { int wm, wn, tmw, tnw, xb, d; };
 constexpr Variant kVariants[] = {
-    {4, 1, 4, 2, 1}, {4, 1, 2, 2, 1}, {2, 1, 4, 2, 1},                      // 0-2: 32 columns
-    {4, 1, 4, 4, 1}, {4, 1, 2, 4, 1}, {2, 1, 4, 4, 1},                      // 3-5: 64 columns
-    {2, 2, 4, 4, 1}, {4, 2, 2, 4, 1}, {4, 2, 4, 4, 1}, {2, 2, 2, 4, 1},     // 6-9: 128 columns
-    {2, 4, 4, 4, 1},                                                        // 10: 256 columns
-    {4, 1, 4, 2, 2}, {4, 1, 4, 4, 2}, {4, 2, 4, 4, 2}, {2, 1, 4, 2, 2},     // 11-14: double-buffered halo
+    {4, 1, 4, 2, 1, 2}, {4, 1, 2, 2, 1, 2}, {2, 1, 4, 2, 1, 2},                         // 0-2: 32 columns
+    {4, 1, 4, 4, 1, 2}, {4, 1, 2, 4, 1, 2}, {2, 1, 4, 4, 1, 2},                         // 3-5: 64 columns
+    {2, 2, 4, 4, 1, 2}, {4, 2, 2, 4, 1, 2}, {4, 2, 4, 4, 1, 2}, {2, 2, 2, 4, 1, 2},     // 6-9: 128 columns
+    {2, 4, 4, 4, 1, 2},                                                                 // 10: 256 columns
+    {4, 1, 4, 2, 2, 2}, {4, 1, 4, 4, 2, 2}, {4, 2, 4, 4, 2, 2}, {2, 1, 4, 2, 2, 2},     // 11-14: double-buffered halo
+    {4, 1, 1, 2, 1, 6}, {2, 1, 1, 2, 1, 6}, {4, 1, 2, 2, 1, 4},                         // 15-17: 64, 32, 128 x 32, deep weight ring
+    {4, 1, 1, 4, 1, 4},                                                                 // 18: 64 x 64, the same
 };
 constexpr int kNumVariants = sizeof(kVariants) / sizeof(kVariants[0]);
 
 #define PVF_VARIANT_CASE(V, TAPS, EPI)                                                                  \
     case V:                                                                                             \
         return run<kVariants[V].wm, kVariants[V].wn, kVariants[V].tmw, kVariants[V].tnw, kVariants[V].xb, \
-                   TAPS, EPI>(a, s);
+                   kVariants[V].d, TAPS, EPI>(a, s);
 
 template <int TAPS, int EPI>
 hipError_t dispatch(int v, const ConvArgs& a, hipStream_t s)
@@ -467,6 +482,10 @@ hipError_t dispatch(int v, const ConvArgs& a, hipStream_t s)
             PVF_VARIANT_CASE(11, TAPS, EPI)
             PVF_VARIANT_CASE(12, TAPS, EPI)
             PVF_VARIANT_CASE(14, TAPS, EPI)
+            PVF_VARIANT_CASE(15, TAPS, EPI)
+            PVF_VARIANT_CASE(16, TAPS, EPI)
+            PVF_VARIANT_CASE(17, TAPS, EPI)
+            PVF_VARIANT_CASE(18, TAPS, EPI)
         default: return hipErrorInvalidValue;
         }
     } else {
@@ -486,6 +505,10 @@ hipError_t dispatch(int v, const ConvArgs& a, hipStream_t s)
             PVF_VARIANT_CASE(12, TAPS, EPI)
             PVF_VARIANT_CASE(13, TAPS, EPI)
             PVF_VARIANT_CASE(14, TAPS, EPI)
+            PVF_VARIANT_CASE(15, TAPS, EPI)
+            PVF_VARIANT_CASE(16, TAPS, EPI)
+            PVF_VARIANT_CASE(17, TAPS, EPI)
+            PVF_VARIANT_CASE(18, TAPS, EPI)
         default: return hipErrorInvalidValue;
         }
     }
@@ -509,7 +532,7 @@ bool f32_variant_ok(int v, int n, int taps, Epi epi)
     const Variant& x = kVariants[v];
     const int bn = x.wn * x.tnw * 16;
     // the head reduces over all channels inside one wave's columns
-    if (epi == EPI_HEAD) return (v <= 3 || v == 5 || v == 11 || v == 12 || v == 14) && bn == n && x.wn == 1;
+    if (epi == EPI_HEAD) return (v <= 3 || v == 5 || v == 11 || v == 12 || (v >= 14 && v <= 18)) && bn == n && x.wn == 1;
     (void)taps;
     return bn <= (n < 32 ? 32 : n);
 }
@@ -528,26 +551,44 @@ int f32_default_variant(int n, int cin, int taps, Epi epi)
     return 7;
 }
 
+// Tiles of small batches, from sweeps of 1 to 200 events of the 32-channel
+// network.  A launch then waits on one block's serial chain of steps, not on
+// throughput, so the smallest tile wins that still keeps every block on the
+// device at once: three blocks a CU of the deep-ring tiles (enc3.c2, one event:
+// 32 x 32 tiles 12 us, 64 x 32 14 us, 128 x 32 23 us, 128 x 128 42 us; eight
+// events, 1008 32 x 32 blocks: 27 us against 19 us with 64 x 32; 16 events, 1008
+// 64 x 32 blocks: 36 us against 31 us with 128 x 32).
+int f32_batch_variant(int full, int n, Epi epi, int m_rows)
+{
+    constexpr int kAtOnce = 3 * 256;
+    if (epi == EPI_HEAD && n == 64) return tile_blocks(m_rows, n, 64, 64) <= kAtOnce ? 18 : full;
+    if (tile_blocks(m_rows, n, 32, 32) <= kAtOnce) return 16;
+    if (tile_blocks(m_rows, n, 64, 32) <= kAtOnce) return 15;
+    if (tile_blocks(m_rows, n, 128, 32) <= kAtOnce) return 17;
+    if (n >= 64 && tile_blocks(m_rows, n, 128, 64) <= kAtOnce) return 4;
+    return full;
+}
+
 std::string f32_kernel_name(int v, int taps, Epi epi)
 {
     const Variant& x = kVariants[v];
     return std::string(x.xb == 2 ? "conv_mfma_f32_db<" : "conv_mfma_f32<") + std::to_string(x.wm) + ", " +
            std::to_string(x.wn) + ", " + std::to_string(x.tmw) + ", " + std::to_string(x.tnw) + ", " +
-           std::to_string(taps) + ", " + std::to_string((int)epi) + ">";
+           (x.xb == 2 ? "" : std::to_string(x.d) + ", ") + std::to_string(taps) + ", " + std::to_string((int)epi) + ">";
 }
 
 // Variants that can take the fused first convolution: the single-buffered
 // tiles of up to 64 columns (enc0.c2 has 32 or 64).
 bool f32_first_ok(int v)
 {
-    return v >= 0 && v <= 5;
+    return (v >= 0 && v <= 5) || (v >= 15 && v <= 17);
 }
 
 std::string f32_first_kernel_name(int v)
 {
     const Variant& x = kVariants[v];
     return "conv_mfma_f32_first<" + std::to_string(x.wm) + ", " + std::to_string(x.wn) + ", " +
-           std::to_string(x.tmw) + ", " + std::to_string(x.tnw) + ">";
+           std::to_string(x.tmw) + ", " + std::to_string(x.tnw) + ", " + std::to_string(x.d) + ">";
 }
 
 hipError_t launch_conv_f32_first(const ConvArgs& a, int v, hipStream_t s)
@@ -555,12 +596,15 @@ hipError_t launch_conv_f32_first(const ConvArgs& a, int v, hipStream_t s)
     if (a.cin % KC != 0 || a.m_rows <= 0 || a.n % 32 != 0 || !f32_first_ok(v) || !f32_variant_ok(v, a.n, kTaps, EPI_POOL))
         return hipErrorInvalidValue;
     switch (v) {
-    case 0: return run_first<kVariants[0].wm, kVariants[0].wn, kVariants[0].tmw, kVariants[0].tnw>(a, s);
-    case 1: return run_first<kVariants[1].wm, kVariants[1].wn, kVariants[1].tmw, kVariants[1].tnw>(a, s);
-    case 2: return run_first<kVariants[2].wm, kVariants[2].wn, kVariants[2].tmw, kVariants[2].tnw>(a, s);
-    case 3: return run_first<kVariants[3].wm, kVariants[3].wn, kVariants[3].tmw, kVariants[3].tnw>(a, s);
-    case 4: return run_first<kVariants[4].wm, kVariants[4].wn, kVariants[4].tmw, kVariants[4].tnw>(a, s);
-    case 5: return run_first<kVariants[5].wm, kVariants[5].wn, kVariants[5].tmw, kVariants[5].tnw>(a, s);
+    case 0: return run_first<kVariants[0].wm, kVariants[0].wn, kVariants[0].tmw, kVariants[0].tnw, kVariants[0].d>(a, s);
+    case 1: return run_first<kVariants[1].wm, kVariants[1].wn, kVariants[1].tmw, kVariants[1].tnw, kVariants[1].d>(a, s);
+    case 2: return run_first<kVariants[2].wm, kVariants[2].wn, kVariants[2].tmw, kVariants[2].tnw, kVariants[2].d>(a, s);
+    case 3: return run_first<kVariants[3].wm, kVariants[3].wn, kVariants[3].tmw, kVariants[3].tnw, kVariants[3].d>(a, s);
+    case 4: return run_first<kVariants[4].wm, kVariants[4].wn, kVariants[4].tmw, kVariants[4].tnw, kVariants[4].d>(a, s);
+    case 5: return run_first<kVariants[5].wm, kVariants[5].wn, kVariants[5].tmw, kVariants[5].tnw, kVariants[5].d>(a, s);
+    case 15: return run_first<kVariants[15].wm, kVariants[15].wn, kVariants[15].tmw, kVariants[15].tnw, kVariants[15].d>(a, s);
+    case 16: return run_first<kVariants[16].wm, kVariants[16].wn, kVariants[16].tmw, kVariants[16].tnw, kVariants[16].d>(a, s);
+    case 17: return run_first<kVariants[17].wm, kVariants[17].wn, kVariants[17].tmw, kVariants[17].tnw, kVariants[17].d>(a, s);
     default: return hipErrorInvalidValue;
     }
 }

@@ -1155,6 +1155,12 @@ constexpr Variant kVariants[] = {
     {2, 1, 4, 2, 32, 6},   // 33: enc0.c2 with the first conv, weight tile straight into LDS (128 x 32)
     {4, 1, 4, 2, 32, 6},   // 34: the same, 256 x 32
     {8, 1, 4, 2, 32, 6},   // 35: the same, 512 x 32
+    {2, 1, 2, 2, 32, 2},   // 36: 64 x 32, double-buffered (128 threads)
+    {2, 1, 1, 2, 32, 2},   // 37: 32 x 32, double-buffered (128 threads)
+    {1, 4, 2, 2, 32, 2},   // 38: 32 x 128, double-buffered
+    {2, 4, 2, 2, 32, 2},   // 39: 64 x 128, double-buffered (512 threads)
+    {1, 2, 2, 2, 32, 2},   // 40: 32 x 64, double-buffered (128 threads)
+    {2, 2, 2, 2, 32, 2},   // 41: 64 x 64, double-buffered
 };
 constexpr int kNumVariants = sizeof(kVariants) / sizeof(kVariants[0]);
 
@@ -1183,6 +1189,10 @@ hipError_t dispatch(int v, const ConvArgs& a, hipStream_t s)
             PVF_LP_CASE(27)
             PVF_LP_CASE(28)
             PVF_LP_CASE(30)
+            PVF_LP_CASE(38)
+            PVF_LP_CASE(39)
+            PVF_LP_CASE(40)
+            PVF_LP_CASE(41)
         default: return hipErrorInvalidValue;
         }
     } else if constexpr (EPI == EPI_HEAD) {
@@ -1202,6 +1212,8 @@ hipError_t dispatch(int v, const ConvArgs& a, hipStream_t s)
             PVF_LP_CASE(27)
             PVF_LP_CASE(28)
             PVF_LP_CASE(29)
+            PVF_LP_CASE(36)
+            PVF_LP_CASE(37)
         default: return hipErrorInvalidValue;
         }
     } else {
@@ -1237,6 +1249,12 @@ hipError_t dispatch(int v, const ConvArgs& a, hipStream_t s)
             PVF_LP_CASE(30)
         // 33-35 run as the register-staged tile of the same shape when
         // enc0.c2 does not compute the first convolution (calibration)
+            PVF_LP_CASE(36)
+            PVF_LP_CASE(37)
+            PVF_LP_CASE(38)
+            PVF_LP_CASE(39)
+            PVF_LP_CASE(40)
+            PVF_LP_CASE(41)
         case 33: return run<T, 2, 1, 4, 2, 32, 0, TAPS, EPI>(a, s);
         case 34: return run<T, 4, 1, 4, 2, 32, 0, TAPS, EPI>(a, s);
         case 35: return run<T, 8, 1, 4, 2, 32, 0, TAPS, EPI>(a, s);
@@ -1274,11 +1292,11 @@ bool lp_variant_ok(int v, int n, int cin, int taps, Epi epi)
     const int bn = x.wn * x.tnw * 16;
     if (cin % x.kc != 0) return false;
     if (epi == EPI_HEAD)
-        return (v == 0 || v == 1 || v == 4 || v == 5 || v == 11 || v == 13 || v == 14 || v == 16 || v >= 20) &&
+        return (v == 0 || v == 1 || v == 4 || v == 5 || v == 11 || v == 13 || v == 14 || v == 16 || (v >= 20 && v <= 37)) &&
                bn == n && x.wn == 1;
     if (epi == EPI_UP)   // the tile must hold every channel of its rows
         return (v == 1 || v == 2 || v == 3 || v == 4 || v == 9 || v == 12 || v == 13 || v == 15 || v == 19 ||
-                v == 22 || v == 23 || v == 26 || v == 27 || v == 28 || v == 30) && bn == n;
+                v == 22 || v == 23 || v == 26 || v == 27 || v == 28 || v == 30 || v >= 38) && bn == n;
     return bn <= (n < 32 ? 32 : n);
 }
 
@@ -1309,6 +1327,45 @@ int lp_default_up_variant(int n, int cin)
 {
     const int v = n == 64 ? 22 : (n == 128 ? 26 : -1);
     return v >= 0 && lp_variant_ok(v, n, cin, kTaps, EPI_UP) ? v : -1;
+}
+
+// Tiles of small batches, from sweeps of 1 to 1000 events of the 32-channel
+// network in BF16.  A launch then waits on one block's serial chain of stages,
+// so the smallest tile wins while the device holds all its blocks at once; past
+// that the 32-column tiles, until the default has a block for every compute
+// unit twice over.  enc3.c2, launch and its event: one event 8.0 us with
+// 32 x 32 tiles, 8.8 with 64 x 32, 11.4 with 128 x 32, 17.4 with the default
+// 256 x 64; 16 events 14.1 with 64 x 32 and 20.3; 32 events 16.8 with 256 x 32
+// and 22.7; 48 events 22.1 and 24.4; 64 events 27.8 and 26.1, so the default.
+int lp_batch_variant(int full, int n, int cin, Epi epi, int m_rows)
+{
+    constexpr int kCus = 256;
+    int v = full;
+    if (lp_dec0_ok(full)) {
+        // dec0.c1 and the head in one launch: 240 rows a block while that fills at most one round (one event 7.8 us, 8.6 with 496)
+        return tile_blocks(m_rows, n, 240, 32) <= kCus ? 31 : full;
+    } else if (kVariants[full].pf == 6) {
+        // enc0.c2 with the first convolution: blocks of 128, 256 or 512 rows
+        v = tile_blocks(m_rows, n, 128, 32) <= kCus ? 33 : tile_blocks(m_rows, n, 256, 32) <= kCus ? 34 : full;
+    } else if (epi == EPI_UP && n == 64) {
+        // with the transposed conv in the epilogue, all columns in a block: 32,
+        // 64 or 128 rows (one event 2.7 us, 10 with the default 512 x 64; 32 events 9.2 and 12.4)
+        if (tile_blocks(m_rows, n, 32, 64) <= kCus) v = 40;
+        else if (tile_blocks(m_rows, n, 64, 64) <= 2 * kCus) v = 41;
+        else if (tile_blocks(m_rows, n, 128, 64) <= 2 * kCus) v = 4;
+    } else if (epi == EPI_UP && n == 128) {
+        // the same: one event 5.4 us, 16 with the default 256 x 128; 32 events 13.8 and 19
+        if (tile_blocks(m_rows, n, 32, 128) <= kCus) v = 38;
+        else if (tile_blocks(m_rows, n, 64, 128) <= kCus) v = 39;
+        else if (tile_blocks(m_rows, n, 128, 128) <= kCus) v = 15;
+    } else if (epi != EPI_HEAD || n == 32) {
+        if (tile_blocks(m_rows, n, 32, 32) <= 3 * kCus) v = 37;
+        else if (tile_blocks(m_rows, n, 64, 32) <= 4 * kCus) v = 36;
+        else if (epi == EPI_CONVT) v = full;
+        else if (tile_blocks(m_rows, n, 256, 32) <= 2 * kCus) v = 14;
+        else if (tile_blocks(m_rows, n, 256, 32) <= 3 * kCus && n > 32) v = cin % 64 == 0 ? 8 : 29;
+    }
+    return lp_variant_ok(v, n, cin, epi == EPI_CONVT ? 1 : kTaps, epi) ? v : full;
 }
 
 bool lp_dec0_ok(int v) { return v >= 0 && v < kNumVariants && (kVariants[v].pf == 3 || kVariants[v].pf == 5); }

@@ -394,6 +394,7 @@ struct pvf_engine {
         int n = 0, cin = 0, taps = 0, cout = 0;
         Epi epi = EPI_STORE;
         int variant = -1;
+        bool pinned = false;          // variant set by the caller or the autotuner: every batch runs it
         const WeightLayout::Conv* w = nullptr;
         std::vector<int> in_src;      // launches whose stored outputs form this input, in channel order
         size_t col = 0;               // FP8: offsets (floats) into the scales region
@@ -423,32 +424,46 @@ namespace {
 template <class T>
 T* at(pvf_engine* e, size_t off) { return reinterpret_cast<T*>(e->arena + off); }
 
-// Whether launch i (enc0.c2) computes the first convolution in its staging:
-// its tile variant can, and no calibration is running (the calibration reads
-// the first convolution's stored output).
-bool fuses_first(const pvf_engine* e, int i)
+// Tile variant of launch i for a batch of m_rows rows.  A default is the pick
+// for full batches; a batch too small to fill the device with its tiles runs a
+// smaller one.  A variant that the caller or the autotuner set runs always.
+int tile(const pvf_engine* e, int i, int m_rows)
 {
-    return e->conv[i].first && !e->calib_table && conv_first_ok(e->spec.compute_dtype, e->conv[i].variant);
+    const auto& c = e->conv[i];
+    if (c.variant < 0 || c.pinned) return c.variant;
+    const int dt = e->spec.compute_dtype;
+    const bool up = c.up && dt != PVF_FP32 && conv_variant_ok(dt, c.variant, c.n, c.cin, c.taps, EPI_UP);
+    return conv_batch_variant(dt, c.variant, c.n, c.cin, up ? EPI_UP : c.epi, m_rows);
 }
 
-// Whether launch i (a decoder conv2 below the deepest level) runs the
-// transposed conv that follows it in its epilogue: 16-bit and FP8 engines,
-// a tile variant whose tile holds all its output channels, and no
+// Whether launch i (enc0.c2) with tile variant v computes the first
+// convolution in its staging: the variant can, and no calibration is running
+// (the calibration reads the first convolution's stored output).
+bool fuses_first(const pvf_engine* e, int i, int v)
+{
+    return e->conv[i].first && !e->calib_table && conv_first_ok(e->spec.compute_dtype, v);
+}
+
+// Whether launch i (a decoder conv2 below the deepest level) with tile variant
+// v runs the transposed conv that follows it in its epilogue: 16-bit and FP8
+// engines, a tile variant whose tile holds all its output channels, and no
 // calibration running (the calibration reads the stored output).
-bool fuses_up(const pvf_engine* e, int i)
+bool fuses_up(const pvf_engine* e, int i, int v)
 {
     const auto& c = e->conv[i];
     const int dt = e->spec.compute_dtype;
-    return c.up && !e->calib_table && dt != PVF_FP32 && conv_variant_ok(dt, c.variant, c.n, c.cin, c.taps, EPI_UP);
+    return c.up && !e->calib_table && dt != PVF_FP32 && conv_variant_ok(dt, v, c.n, c.cin, c.taps, EPI_UP);
 }
+bool fuses_up(const pvf_engine* e, int i) { return fuses_up(e, i, e->conv[i].variant); }
 
-// Whether launch i (dec0.c2 + head) computes dec0.c1 in the same kernel:
-// 16-bit and FP8 engines, a variant that does, and no calibration running
-// (the calibration reads dec0.c1's stored output).
-bool fuses_dec0(const pvf_engine* e, int i)
+// Whether launch i (dec0.c2 + head) with tile variant v computes dec0.c1 in
+// the same kernel: 16-bit and FP8 engines, a variant that does, and no
+// calibration running (the calibration reads dec0.c1's stored output).
+bool fuses_dec0(const pvf_engine* e, int i, int v)
 {
-    return e->conv[i].dec0 && !e->calib_table && conv_dec0_ok(e->spec.compute_dtype, e->conv[i].variant);
+    return e->conv[i].dec0 && !e->calib_table && conv_dec0_ok(e->spec.compute_dtype, v);
 }
+bool fuses_dec0(const pvf_engine* e, int i) { return fuses_dec0(e, i, e->conv[i].variant); }
 
 // Kernel names of dec0.c1 and dec0.c2 + head for the head's current variant.
 void name_dec0(pvf_engine* e)
@@ -759,7 +774,6 @@ pvf_status enqueue(pvf_engine* eng, const pvf_tracks* tr, const pvf_vertices* ou
         if (eng->profiling && err == hipSuccess) err = hipEventRecord(eng->events[li + 1], s);
         ++li;
     };
-    auto var = [&]() { return eng->conv[li].variant; };
 
     // ---- FC stage: tracks -> scaled histogram rows of level 0
     TrackArgs ta{};
@@ -819,9 +833,9 @@ pvf_status enqueue(pvf_engine* eng, const pvf_tracks* tr, const pvf_vertices* ou
         }
         const int C = eng->conv[li].cout;
         if (a.first_x0)
-            check(launch_conv_first(dt, a, var(), s));
+            check(launch_conv_first(dt, a, tile(eng, li, a.m_rows), s));
         else
-            check(launch_conv(dt, a, taps, epi, var(), s));
+            check(launch_conv(dt, a, taps, epi, tile(eng, li, a.m_rows), s));
         if (epi != EPI_HEAD) {
             // a.out points at the tensor's first channel; the calibration reads
             // whole rows from the buffer start with the channel offset
@@ -832,7 +846,7 @@ pvf_status enqueue(pvf_engine* eng, const pvf_tracks* tr, const pvf_vertices* ou
 
     // ---- encoder
     const int first_li = li;          // enc0.c1
-    const bool fused = fuses_first(eng, first_li + 1);
+    const bool fused = fuses_first(eng, first_li + 1, tile(eng, first_li + 1, EU * P.lv[0].R));
     if (fused) {
         check(hipSuccess);            // enc0.c2 computes it in its staging
     } else {
@@ -890,12 +904,13 @@ pvf_status enqueue(pvf_engine* eng, const pvf_tracks* tr, const pvf_vertices* ou
             conv(u, 1, EPI_CONVT, l, 2 * lv.C, lv.C);
         }
         const ConvArgs c1 = conv_args(eng, W.dec[l][0], act(P.cat[l]), 2 * lv.C, lv.R, EU, act(P.a[l]), lv.C);
-        const bool dec0 = l == 0 && fuses_dec0(eng, li + 1);
+        const int head_v = l == 0 ? tile(eng, li + 1, c1.m_rows) : -1;
+        const bool dec0 = l == 0 && fuses_dec0(eng, li + 1, head_v);
         if (dec0) check(hipSuccess);  // computed inside the head launch
         else conv(c1, kTaps, EPI_STORE, l, lv.C, 0);
         if (l > 0) {
             ConvArgs c2 = conv_args(eng, W.dec[l][1], act(P.a[l]), lv.C, lv.R, EU, act(P.d[l]), lv.C);
-            up_done = fuses_up(eng, li);
+            up_done = fuses_up(eng, li, tile(eng, li, c2.m_rows));
             if (up_done) {
                 // up(l - 1) on this launch's output tiles: its weights, bias
                 // and destination (the upsampled half of level l - 1's concat)
@@ -931,8 +946,8 @@ pvf_status enqueue(pvf_engine* eng, const pvf_tracks* tr, const pvf_vertices* ou
                     d1.fold_bias = scales + eng->conv[li - 1].fold + eng->conv[li - 1].n;
                     b.col_scale = scales + eng->conv[li].col;
                 }
-                check(launch_conv_dec0(dt, d1, b, var(), s));
-            } else if (eng->conv[li].dec0 && conv_dec0_ok(dt, var())) {
+                check(launch_conv_dec0(dt, d1, b, head_v, s));
+            } else if (eng->conv[li].dec0 && conv_dec0_ok(dt, head_v)) {
                 // a fused variant while calibrating: dec0.c1 ran on its own,
                 // and the head takes the default tile
                 check(launch_conv(dt, b, kTaps, EPI_HEAD, conv_default_variant(dt, b.n, b.cin, kTaps, EPI_HEAD), s));
@@ -1231,6 +1246,7 @@ pvf_status pvf_set_launch_variant(pvf_engine* eng, int i, int v)
     auto& c = eng->conv[i];
     if (!conv_variant_ok(eng->spec.compute_dtype, v, c.n, c.cin, c.taps, c.epi)) return PVF_ERR_INVALID_ARGUMENT;
     c.variant = v;
+    c.pinned = true;
     eng->kernels[i] = conv_kernel_name(eng->spec.compute_dtype, v, c.cin, c.taps, c.epi);
     name_first(eng);
     name_up(eng);
@@ -1256,6 +1272,7 @@ pvf_status pvf_autotune(pvf_engine* eng, const pvf_tracks* tr, const pvf_vertice
         for (int i = 0; i < nl; ++i) {
             auto& c = eng->conv[i];
             if (c.variant < 0) continue;
+            c.pinned = true;
             if (conv_variant_ok(eng->spec.compute_dtype, v, c.n, c.cin, c.taps, c.epi)) { c.variant = v; any = true; }
             else c.variant = saved[i].variant;
         }

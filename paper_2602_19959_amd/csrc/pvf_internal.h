@@ -277,6 +277,13 @@ std::string conv_first_kernel_name(int dtype, int variant);
 int conv_variant_count(int dtype);
 bool conv_variant_ok(int dtype, int variant, int n, int cin, int taps, Epi epi);
 int conv_default_variant(int dtype, int n, int cin, int taps, Epi epi);
+// Variant to run in place of the default `full` for a batch of m_rows rows:
+// a smaller tile while the default's would leave compute units idle.  epi:
+// EPI_UP where the default runs the next transposed conv in its epilogue (as
+// the variant returned does then).
+int conv_batch_variant(int dtype, int full, int n, int cin, Epi epi, int m_rows);
+// Blocks of a bm x bn tiling of m_rows x n outputs
+inline int64_t tile_blocks(int m_rows, int n, int bm, int bn) { return ((int64_t)m_rows + bm - 1) / bm * ((n + bn - 1) / bn); }
 // Default tile variant of a 5-tap launch that runs the transposed conv after
 // it in its epilogue (EPI_UP), or -1 where no variant of the dtype can.
 int conv_default_up_variant(int dtype, int n, int cin);
@@ -293,6 +300,7 @@ hipError_t launch_split_weights(const float* w, int n, int taps, int cin, uint16
 int f32_variant_count();
 bool f32_variant_ok(int variant, int n, int taps, Epi epi);
 int f32_default_variant(int n, int cin, int taps, Epi epi);
+int f32_batch_variant(int full, int n, Epi epi, int m_rows);
 std::string f32_kernel_name(int variant, int taps, Epi epi);
 hipError_t launch_conv_f32_first(const ConvArgs& a, int variant, hipStream_t s);
 bool f32_first_ok(int variant);
@@ -301,6 +309,7 @@ hipError_t launch_conv_lp(int dtype, const ConvArgs& a, int taps, Epi epi, int v
 int lp_variant_count();
 bool lp_variant_ok(int variant, int n, int cin, int taps, Epi epi);
 int lp_default_variant(int n, int cin, int taps, Epi epi);
+int lp_batch_variant(int full, int n, int cin, Epi epi, int m_rows);
 std::string lp_kernel_name(int dtype, int variant, int taps, Epi epi);
 hipError_t launch_conv_lp_first(int dtype, const ConvArgs& a, int variant, hipStream_t s);
 bool lp_first_ok(int variant);
@@ -326,6 +335,7 @@ hipError_t launch_conv_fp8(const ConvArgs& a, int taps, Epi epi, int variant, hi
 int fp8_variant_count();
 bool fp8_variant_ok(int variant, int n, int cin, int taps, Epi epi);
 int fp8_default_variant(int n, int cin, int taps, Epi epi);
+int fp8_batch_variant(int full, int n, int cin, Epi epi, int m_rows);
 std::string fp8_kernel_name(int variant, int cin, int taps, Epi epi);
 
 inline int act_bytes(int dtype) { return dtype == PVF_FP32 ? 4 : (dtype == PVF_FP8_E4M3 ? 1 : 2); }
