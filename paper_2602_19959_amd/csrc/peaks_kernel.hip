@@ -30,11 +30,15 @@
 namespace pvf {
 namespace {
 
-constexpr int NT = 256;
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 constexpr int kQ = 4;            // bins per thread and round in the candidate pass
-constexpr int kMaxRounds = 16;   // bins per event <= kQ * NT * kMaxRounds (kQ bits per round)
-constexpr int kMaxList = 32;     // rounds of the candidate list (at most half the bins)
+constexpr int kMaxBins = 16384;  // bins per event
+// Rounds of a block of NT threads: over the bins (kQ bits of a 64-bit mask per
+// round), and over the candidate list (at most half the bins).
+template <int NT> struct Rounds {
+    static constexpr int bins = kMaxBins / (kQ * NT);
+    static constexpr int list = kMaxBins / 2 / NT;
+};
 
 // S = sum of p over the window [t - hw, t + hw] clipped to the row, M = sum
 // of p times the bin centre, both accumulated in double in ascending bin
@@ -73,7 +77,7 @@ __device__ __forceinline__ void window(const float* ps, int t, int L, const Peak
 
 // Sum of the per-wave counts of round k over all waves, and over the waves
 // before this one.
-template <int R>
+template <int NT, int R>
 __device__ __forceinline__ void round_counts(const int (*cnt)[R], int k, int wave, int& before, int& all)
 {
     before = 0;
@@ -86,12 +90,14 @@ __device__ __forceinline__ void round_counts(const int (*cnt)[R], int k, int wav
     }
 }
 
-template <int HW>
+// NT = 256: up to eight blocks share a CU, for batches that fill the device;
+// NT = 1024: a quarter of the rounds, for batches that do not.
+template <int HW, int NT>
 __global__ __launch_bounds__(NT) void peak_finder(PeakArgs a)
 {
     extern __shared__ __attribute__((aligned(16))) float ps[];   // [L] row, then the candidate list
-    __shared__ int ccount[NT / 64][kMaxRounds];   // candidates per wave and round
-    __shared__ int vcount[NT / 64][kMaxList];     // vertices per wave and list round
+    __shared__ int ccount[NT / 64][Rounds<NT>::bins];   // candidates per wave and round
+    __shared__ int vcount[NT / 64][Rounds<NT>::list];     // vertices per wave and list round
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int e = blockIdx.x;
@@ -146,7 +152,7 @@ __global__ __launch_bounds__(NT) void peak_finder(PeakArgs a)
     int nc = 0;
     for (int k = 0; k < rounds; ++k) {
         int before, all;
-        round_counts<kMaxRounds>(ccount, k, wave, before, all);
+        round_counts<NT, Rounds<NT>::bins>(ccount, k, wave, before, all);
         const unsigned bits = (unsigned)(mine >> (kQ * k)) & ((1u << kQ) - 1u);
         int rank = nc + before;                   // candidates before this thread's first one
 #pragma unroll
@@ -183,7 +189,7 @@ __global__ __launch_bounds__(NT) void peak_finder(PeakArgs a)
     int nv = 0;
     for (int r = 0; r < crounds; ++r) {
         int before, all;
-        round_counts<kMaxList>(vcount, r, wave, before, all);
+        round_counts<NT, Rounds<NT>::list>(vcount, r, wave, before, all);
         const bool ok = (vmine >> r) & 1ull;
         const uint64_t m = __ballot(ok);
         const int slot = nv + before + __popcll(m & below);
@@ -204,17 +210,25 @@ __global__ __launch_bounds__(NT) void peak_finder(PeakArgs a)
     }
 }
 
+// One block a compute unit: 1024 threads (one event 7 us, 10.5 with 256; 200
+// events 10 and 14; 300 events 17 either way).
+constexpr int kWideEvents = 256;
+
 }  // namespace
 
 hipError_t launch_peaks(const PeakArgs& a, int n_events, hipStream_t s)
 {
     // strict local maxima are never adjacent: at most L / 2 candidates
-    if (a.L < 3 || a.L > kQ * NT * kMaxRounds || a.hw < 0) return hipErrorInvalidValue;
+    if (a.L < 3 || a.L > kMaxBins || a.hw < 0) return hipErrorInvalidValue;
     const size_t lds = sizeof(float) * a.L + sizeof(uint16_t) * (a.L / 2 + 1);
-    if (a.hw == 5)
-        hipLaunchKernelGGL(peak_finder<5>, dim3(n_events), dim3(NT), lds, s, a);
-    else
-        hipLaunchKernelGGL(peak_finder<-1>, dim3(n_events), dim3(NT), lds, s, a);
+    const bool wide = n_events <= kWideEvents;
+    if (a.hw == 5) {
+        if (wide) hipLaunchKernelGGL((peak_finder<5, 1024>), dim3(n_events), dim3(1024), lds, s, a);
+        else hipLaunchKernelGGL((peak_finder<5, 256>), dim3(n_events), dim3(256), lds, s, a);
+    } else {
+        if (wide) hipLaunchKernelGGL((peak_finder<-1, 1024>), dim3(n_events), dim3(1024), lds, s, a);
+        else hipLaunchKernelGGL((peak_finder<-1, 256>), dim3(n_events), dim3(256), lds, s, a);
+    }
     return hipGetLastError();
 }
 

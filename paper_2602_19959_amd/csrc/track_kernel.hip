@@ -115,21 +115,22 @@ __device__ __forceinline__ void features(const TrackArgs& a, const float* f, dou
     for (int k = 1; k < kFeat; ++k) g[k] = (f[k] - a.shift[k]) * a.scale[k];
 }
 
-// Item t of an event (t < end): its interval (-1 when it is dropped: outside
+// An event's item with features f: its interval (-1 when it is dropped: outside
 // the window or not finite), its network inputs g in that interval's frame,
 // and the neighbouring interval it also feeds (-1 if none); the binning
 // compares with the exact interval edges in double.  A dropped item sets
 // *dropped (a benign race: every writer stores 1).
-__device__ __forceinline__ void bin_track(const TrackArgs& a, int64_t t, double z_max, bool two, int& itv, int& nb,
+__device__ __forceinline__ void load_track(const TrackArgs& a, int64_t t, float* f)
+{
+#pragma unroll
+    for (int k = 0; k < kFeat; ++k) f[k] = a.feat[k][t];
+}
+__device__ __forceinline__ void bin_track(const TrackArgs& a, const float* f, double z_max, bool two, int& itv, int& nb,
                                           float* g, int* dropped)
 {
-    float f[kFeat];
     bool finite = true;
 #pragma unroll
-    for (int k = 0; k < kFeat; ++k) {
-        f[k] = a.feat[k][t];
-        finite = finite && isfinite(f[k]);
-    }
+    for (int k = 0; k < kFeat; ++k) finite = finite && isfinite(f[k]);
     const double zd = (double)f[0];
     if (finite && zd >= a.z_min && zd < z_max) {
         int i = (int)floor((zd - a.z_min) / a.interval_mm);
@@ -232,7 +233,14 @@ template <> struct Net<_Float16> {
     using V = f16x8;
     static constexpr int KP = 40;
     __device__ static f32x4 mfma(V x, V w, f32x4 c) { return __builtin_amdgcn_mfma_f32_16x16x32_f16(x, w, c, 0, 0, 0); }
-    __device__ static _Float16 cvt(float v, float) { return (_Float16)v; }
+    // the rounding to FP32 stays: without the barrier the compiler may merge the
+    // operation before it into v_fma_mixlo_f16, in one form of the kernel and
+    // not in another
+    __device__ static _Float16 cvt(float v, float)
+    {
+        asm("" : "+v"(v));
+        return (_Float16)v;
+    }
 };
 template <> struct Net<uint8_t> {
     using V = long;
@@ -256,60 +264,87 @@ __device__ __forceinline__ const float* layer_bias(const TrackArgs& a, int l)
 template <class E>
 __device__ __forceinline__ void store_inputs(const TrackArgs& a, E* xa, int row, const float* g)
 {
+    constexpr int PER = 16 / (int)sizeof(E);       // elements of a 16-byte store
     E* r = xa + row * Net<E>::KP;
 #pragma unroll
-    for (int k = 0; k < kMlpK; ++k) {
-        const float inv = (sizeof(E) == 1 && k < kFeat) ? a.mlp_in_inv[k] : 1.f;
-        r[k] = Net<E>::cvt(k < kFeat ? g[k] : 0.f, inv);
+    for (int c = 0; c < kMlpK / PER; ++c) {
+        E y[PER];
+#pragma unroll
+        for (int q = 0; q < PER; ++q) {
+            const int k = c * PER + q;
+            const float inv = (sizeof(E) == 1 && k < kFeat) ? a.mlp_in_inv[k] : 1.f;
+            y[q] = Net<E>::cvt(k < kFeat ? g[k] : 0.f, inv);
+        }
+        *reinterpret_cast<uint4*>(r + c * PER) = *reinterpret_cast<const uint4*>(y);
     }
 }
 
-// Hidden layers of the wave's 64 rows, in place in xa.
-template <class E>
-__device__ void hidden_layers_mma(const TrackArgs& a, E* xa, const int* iv, int wave, int lane)
+// Hidden layers of TW tiles of 16 rows, STRIDE rows apart from row0 on, in
+// place in xa.  PRE: the next layer's weights are on their way while a layer
+// runs (28 registers, which the form with four blocks a CU does not have).
+template <class E, int TW, int STRIDE, bool PRE>
+__device__ void hidden_layers_mma(const TrackArgs& a, E* xa, const int* iv, int row0, int lane)
 {
     using V = typename Net<E>::V;
     constexpr int KP = Net<E>::KP;
     const int li = lane & 15, lg = lane >> 4;
     const E* wp = static_cast<const E*>(a.mlp_lp);
-    E* rows = xa + (size_t)wave * 64 * KP;
-    const int* kept = iv + wave * 64 + 4 * lg;   // kept[16 i + v] >= 0: row 16 i + 4 lg + v is a kept item
-    for (int l = 0; l < a.n_hidden; ++l) {
+    E* rows = xa + (size_t)row0 * KP;
+    const int* kept = iv + row0 + 4 * lg;   // kept[STRIDE i + v] >= 0: row STRIDE i + 4 lg + v is a kept item
+    struct Layer { V w[2]; float cs[2], bn[2], inv[2]; };
+    auto load = [&](int l) __attribute__((always_inline)) {
+        Layer L;
         const E* W = wp + (size_t)l * kMlpHiddenN * kMlpK;
         const float* b = layer_bias(a, l);
-        V x[4], w[2];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) x[i] = *reinterpret_cast<const V*>(rows + (16 * i + li) * KP + 8 * lg);
-#pragma unroll
-        for (int j = 0; j < 2; ++j) w[j] = *reinterpret_cast<const V*>(W + (16 * j + li) * kMlpK + 8 * lg);
-        f32x4 acc[4][2];
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-#pragma unroll
-            for (int j = 0; j < 2; ++j) acc[i][j] = Net<E>::mfma(x[i], w[j], f32x4{0.f, 0.f, 0.f, 0.f});
-        __builtin_amdgcn_wave_barrier();
 #pragma unroll
         for (int j = 0; j < 2; ++j) {
             const int n = 16 * j + li;                        // output channel of this lane
             const bool used = n < kHidden;
-            const float cs = (sizeof(E) == 1 && used) ? a.mlp_col[l * kMlpHiddenN + n] : 1.f;
-            const float bn = used ? b[n] : 0.f;
-            const float inv = (sizeof(E) == 1 && used) ? a.mlp_in_inv[(l + 1) * kMlpK + n] : 1.f;
+            L.w[j] = *reinterpret_cast<const V*>(W + n * kMlpK + 8 * lg);
+            L.cs[j] = (sizeof(E) == 1 && used) ? a.mlp_col[l * kMlpHiddenN + n] : 1.f;
+            L.bn[j] = used ? b[n] : 0.f;
+            L.inv[j] = (sizeof(E) == 1 && used) ? a.mlp_in_inv[(l + 1) * kMlpK + n] : 1.f;
+        }
+        return L;
+    };
+    Layer cur, next;
+    if (PRE) next = load(0);
+    for (int l = 0; l < a.n_hidden; ++l) {
+        if (PRE) {
+            cur = next;
+            next = load(min(l + 1, a.n_hidden - 1));
+        } else {
+            cur = load(l);
+        }
+        V x[TW];
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
+        for (int i = 0; i < TW; ++i) x[i] = *reinterpret_cast<const V*>(rows + (STRIDE * i + li) * KP + 8 * lg);
+        f32x4 acc[TW][2];
+#pragma unroll
+        for (int i = 0; i < TW; ++i)
+#pragma unroll
+            for (int j = 0; j < 2; ++j) acc[i][j] = Net<E>::mfma(x[i], cur.w[j], f32x4{0.f, 0.f, 0.f, 0.f});
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            const int n = 16 * j + li;
+            const bool used = n < kHidden;
+            const float cs = cur.cs[j], bn = cur.bn[j], inv = cur.inv[j];
+#pragma unroll
+            for (int i = 0; i < TW; ++i)
 #pragma unroll
                 for (int v = 0; v < 4; ++v) {
                     const float y = used ? lrelu(acc[i][j][v] * cs + bn, a.slope) : 0.f;
-                    rows[(16 * i + 4 * lg + v) * KP + n] = Net<E>::cvt(y, inv);
+                    rows[(STRIDE * i + 4 * lg + v) * KP + n] = Net<E>::cvt(y, inv);
                 }
             if (a.mlp_calib) {
                 // the largest |output| over the wave's kept items
                 float m = 0.f;
 #pragma unroll
-                for (int i = 0; i < 4; ++i)
+                for (int i = 0; i < TW; ++i)
 #pragma unroll
                     for (int v = 0; v < 4; ++v)
-                        if (kept[16 * i + v] >= 0) m = fmaxf(m, fabsf(used ? lrelu(acc[i][j][v] * cs + bn, a.slope) : 0.f));
+                        if (kept[STRIDE * i + v] >= 0) m = fmaxf(m, fabsf(used ? lrelu(acc[i][j][v] * cs + bn, a.slope) : 0.f));
                 m = fmaxf(m, __shfl_xor(m, 16));
                 m = fmaxf(m, __shfl_xor(m, 32));
                 if (lg == 0 && used)
@@ -419,7 +454,7 @@ __device__ void track_event(const TrackArgs& a, int e, float* smem)
                 for (int k = 0; k < kFeat; ++k) wave_amax(a.mlp_calib + calib_off(0) + k, z[k]);
             store_inputs<E>(a, xa, tid, z);
             __builtin_amdgcn_wave_barrier();
-            if (any) hidden_layers_mma<E>(a, xa, iv, wave, lane);
+            if (any) hidden_layers_mma<E, 4, 16, false>(a, xa, iv, 64 * wave, lane);
         }
     };
 
@@ -510,7 +545,11 @@ __device__ void track_event(const TrackArgs& a, int e, float* smem)
             float g[kFeat];
 #pragma unroll
             for (int k = 0; k < kFeat; ++k) g[k] = 0.f;
-            if (t < end) bin_track(a, t, z_max, two, itv, nb, g, &dropped_any);
+            if (t < end) {
+                float f[kFeat];
+                load_track(a, t, f);
+                bin_track(a, f, z_max, two, itv, nb, g, &dropped_any);
+            }
             iv[tid] = itv;   // read by the hidden layers' calibration
             network_hidden(g, itv >= 0);
             nbv[tid] = nb;
@@ -622,16 +661,16 @@ constexpr float kBf16Max = 0x1.fcp127f;     // largest finite BF16
 
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
-// One-hot A operand of interval m for K step s: element u is 1 when the
-// lane's item (2 s + u / 4, u % 4) lies in interval m.
-__device__ __forceinline__ bf16x8 onehot(const int (&itv)[4][4], int s, int m)
+// One-hot A operand of interval m for a K step: element u is 1 when the
+// lane's item (u / 4, u % 4) of the step lies in interval m.
+__device__ __forceinline__ bf16x8 onehot(const int (&itv)[2][4], int m)
 {
     u32x4 r;
 #pragma unroll
     for (int p = 0; p < 4; ++p) {
         const int u0 = 2 * p, u1 = 2 * p + 1;
-        const bool e0 = itv[2 * s + u0 / 4][u0 % 4] == m;
-        const bool e1 = itv[2 * s + u1 / 4][u1 % 4] == m;
+        const bool e0 = itv[u0 / 4][u0 % 4] == m;
+        const bool e1 = itv[u1 / 4][u1 % 4] == m;
         r[p] = (e0 ? 0x3F80u : 0u) | (e1 ? 0x3F800000u : 0u);
     }
     return __builtin_bit_cast(bf16x8, r);
@@ -642,28 +681,36 @@ __device__ __forceinline__ f32x4 mfma_bf16(bf16x8 x, bf16x8 w, f32x4 c)
     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(x, w, c, 0, 0, 0);
 }
 
-// Column tiles of wave `wave` in block `blk`: q and q + 4, q = (wave + blk) % 4
-// (the tile count is odd, so the rotation spreads the lighter wave over the
-// SIMDs of a CU).
-__device__ __forceinline__ int hist_tile(int wave, int blk, int jl) { return ((wave + blk) & 3) + 4 * jl; }
+// First column tile of wave `wave` in block `blk`.  Four waves take two tiles
+// each, q and q + 4, q = (wave + blk) % 4 (the tile count is odd, so the
+// rotation spreads the lighter wave over the SIMDs of a CU); eight take one
+// each.  part: the half of the tiles that an eight-wave block computes with four of
+// its waves when two blocks share an event, or -1.
+template <int NW>
+__device__ __forceinline__ int hist_tile(int wave, int blk, int part)
+{
+    if (NW == 8 && part >= 0) return wave < 4 ? 4 * part + wave : kMlpOutN / 16;
+    return (wave + blk) & (NW - 1);
+}
 
 // Outputs of items [0, n) of the chunk for the wave's column tiles, added to
 // the wave's histogram tiles h[column tile][interval tile].
-template <class E>
-__device__ void outputs_to_hist(const TrackArgs& a, const E* xa, const int* iv, int n, int wave, int lane,
-                                f32x4 (&h)[2][kRegMT])
+template <class E, int NW>
+__device__ void outputs_to_hist(const TrackArgs& a, const E* xa, const int* iv, int n, int jt0, int lane,
+                                f32x4 (&h)[8 / NW][kRegMT])
 {
+    constexpr int JL = 8 / NW;
     using V = typename Net<E>::V;
     constexpr int KP = Net<E>::KP;
     const int li = lane & 15, lg = lane >> 4;
     const E* W = static_cast<const E*>(a.mlp_lp) + (size_t)a.n_hidden * kMlpHiddenN * kMlpK;
     const float* b = layer_bias(a, a.n_hidden);
-    bool on[2];
-    V w[2];
-    float cs[2], bn[2];
+    bool on[JL];
+    V w[JL];
+    float cs[JL], bn[JL];
 #pragma unroll
-    for (int jl = 0; jl < 2; ++jl) {
-        const int jt = hist_tile(wave, blockIdx.x, jl);
+    for (int jl = 0; jl < JL; ++jl) {
+        const int jt = jt0 + 4 * jl;
         on[jl] = jt < kMlpOutN / 16 && 16 * jt < a.n_out;
         const int c = on[jl] ? 16 * jt + li : li;
         w[jl] = *reinterpret_cast<const V*>(W + (size_t)c * kMlpK + 8 * lg);
@@ -677,23 +724,23 @@ __device__ void outputs_to_hist(const TrackArgs& a, const E* xa, const int* iv, 
         for (int s = 0; s < 2; ++s) {
             // the lane's items 16 i + 4 lg + v, i = 2 s, 2 s + 1: intervals,
             // layer inputs, and the one-hot operand of each interval tile
-            int itv[4][4];
+            int itv[2][4];
             V x[2];
 #pragma unroll
             for (int ii = 0; ii < 2; ++ii) {
                 const int i = 2 * s + ii;
                 x[ii] = *reinterpret_cast<const V*>(xa + (size_t)(sub + 16 * i + li) * KP + 8 * lg);
                 const int4 q = *reinterpret_cast<const int4*>(iv + sub + 16 * i + 4 * lg);
-                itv[i][0] = q.x;
-                itv[i][1] = q.y;
-                itv[i][2] = q.z;
-                itv[i][3] = q.w;
+                itv[ii][0] = q.x;
+                itv[ii][1] = q.y;
+                itv[ii][2] = q.z;
+                itv[ii][3] = q.w;
             }
             bf16x8 oh[kRegMT];
 #pragma unroll
-            for (int mt = 0; mt < kRegMT; ++mt) oh[mt] = onehot(itv, s, 16 * mt + li);
+            for (int mt = 0; mt < kRegMT; ++mt) oh[mt] = onehot(itv, 16 * mt + li);
 #pragma unroll
-            for (int jl = 0; jl < 2; ++jl) {
+            for (int jl = 0; jl < JL; ++jl) {
                 if (!on[jl]) continue;
                 // y = t0 + t1 + r with t0 = bf16(y), t1 = bf16(y - t0), |r| <= 2^-16 |y|
                 bf16x8 t0, t1;
@@ -719,58 +766,83 @@ __device__ void outputs_to_hist(const TrackArgs& a, const E* xa, const int* iv, 
     }
 }
 
-// FP32 hidden layers on the matrix cores (v_mfma_f32_16x16x4_f32) for the
-// wave's 64 rows of hb, in place: K step s of row tile i gives lane (lg, li)
-// element k = 4 s + lg of row 16 i + li (zero past the layer's inputs) and
-// of channel 16 j + li's weights; bias and LeakyReLU in FP32 on the way back.
+// FP32 hidden layers on the matrix cores (v_mfma_f32_16x16x4_f32) for TW tiles
+// of 16 rows of hb, STRIDE rows apart from row0 on, in place: K step s of
+// row tile i gives lane (lg, li) element k = 4 s + lg of row li of the tile
+// (zero past the layer's inputs) and of channel 16 j + li's weights; bias and
+// LeakyReLU in FP32 on the way back.  UNROLL tiles at a time: their outputs
+// replace their inputs (the tiles' reads come first in the wave's program
+// order).  PRE as above.
 // Calibration: each layer's per-channel output maximum over the wave's kept
 // rows (iv >= 0), the quantity the vector-ALU form measures.
-__device__ void hidden_layers_f32_mma(const TrackArgs& a, float* hb, const int* iv, int wave, int lane)
+template <int TW, int STRIDE, int UNROLL, bool PRE>
+__device__ void hidden_layers_f32_mma(const TrackArgs& a, float* hb, const int* iv, int row0, int lane)
 {
     const int li = lane & 15, lg = lane >> 4;
-    float* rows = hb + (size_t)wave * 64 * HPM;
+    float* rows = hb + (size_t)row0 * HPM;
     const float* Wh = a.mlp + kHidden * kFeat + kHidden;   // hidden layers 2.. : [W 20x20, b 20]
     constexpr int KS = kHidden / 4;
-    const int* kept = iv + wave * 64 + 4 * lg;   // kept[16 i + v] >= 0: row 16 i + 4 lg + v is a kept item
-    for (int l = 0; l < a.n_hidden; ++l) {
+    const int* kept = iv + row0 + 4 * lg;   // kept[STRIDE i + v] >= 0: row STRIDE i + 4 lg + v is a kept item
+    struct Layer { float w[2][KS], bn[2]; };
+    auto load = [&](int l) __attribute__((always_inline)) {
+        Layer L;
         const int K = l == 0 ? kFeat : kHidden;
         const float* W = l == 0 ? a.mlp : Wh + (size_t)(l - 1) * (kHidden * kHidden + kHidden);   // [20][K]
         const float* b = W + kHidden * K;
-        float w[2][KS], bn[2], m[2] = {0.f, 0.f};
 #pragma unroll
         for (int j = 0; j < 2; ++j) {
             const int c = 16 * j + li;
 #pragma unroll
             for (int ks = 0; ks < KS; ++ks) {
                 const int k = 4 * ks + lg;
-                w[j][ks] = (c < kHidden && k < K) ? W[c * K + k] : 0.f;
+                L.w[j][ks] = (c < kHidden && k < K) ? W[c * K + k] : 0.f;
             }
-            bn[j] = c < kHidden ? b[c] : 0.f;
+            L.bn[j] = c < kHidden ? b[c] : 0.f;
         }
-        // one row tile at a time: its outputs replace its inputs (the tile's
-        // reads come first in the wave's program order), so only that tile's
-        // accumulators are live
+        return L;
+    };
+    Layer cur, next;
+    if (PRE) next = load(0);
+    for (int l = 0; l < a.n_hidden; ++l) {
+        if (PRE) {
+            cur = next;
+            next = load(min(l + 1, a.n_hidden - 1));
+        } else {
+            cur = load(l);
+        }
+        const int K = l == 0 ? kFeat : kHidden;
+        float m[2] = {0.f, 0.f};
 #pragma unroll 1
-        for (int i = 0; i < 4; ++i) {
-            f32x4 acc[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
+        for (int i0 = 0; i0 < TW; i0 += UNROLL) {
+            f32x4 acc[UNROLL][2];
+#pragma unroll
+            for (int u = 0; u < UNROLL; ++u)
+#pragma unroll
+                for (int j = 0; j < 2; ++j) acc[u][j] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
             for (int ks = 0; ks < KS; ++ks) {
                 if (4 * ks >= K) break;
                 const int k = 4 * ks + lg;
-                const float x = k < K ? rows[(16 * i + li) * HPM + k] : 0.f;
 #pragma unroll
-                for (int j = 0; j < 2; ++j) acc[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(x, w[j][ks], acc[j], 0, 0, 0);
-            }
+                for (int u = 0; u < UNROLL; ++u) {
+                    const float x = k < K ? rows[(STRIDE * (i0 + u) + li) * HPM + k] : 0.f;
 #pragma unroll
-            for (int j = 0; j < 2; ++j) {
-                const int c = 16 * j + li;
-#pragma unroll
-                for (int v = 0; v < 4; ++v) {
-                    const float y = lrelu(acc[j][v] + bn[j], a.slope);
-                    if (c < kHidden) rows[(16 * i + 4 * lg + v) * HPM + c] = y;
-                    if (a.mlp_calib && kept[16 * i + v] >= 0) m[j] = fmaxf(m[j], fabsf(y));
+                    for (int j = 0; j < 2; ++j)
+                        acc[u][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(x, cur.w[j][ks], acc[u][j], 0, 0, 0);
                 }
             }
+#pragma unroll
+            for (int u = 0; u < UNROLL; ++u)
+#pragma unroll
+                for (int j = 0; j < 2; ++j) {
+                    const int c = 16 * j + li;
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) {
+                        const float y = lrelu(acc[u][j][v] + cur.bn[j], a.slope);
+                        if (c < kHidden) rows[(STRIDE * (i0 + u) + 4 * lg + v) * HPM + c] = y;
+                        if (a.mlp_calib && kept[STRIDE * (i0 + u) + v] >= 0) m[j] = fmaxf(m[j], fabsf(y));
+                    }
+                }
         }
         if (a.mlp_calib) {
             // the largest |output| over the wave's kept items
@@ -794,8 +866,9 @@ __device__ void hidden_layers_f32_mma(const TrackArgs& a, float* hb, const int* 
 // gives item 16 i + 4 lg + v, whose output the lane holds in acc[v] (the B
 // operand as it stands) and whose one-hot entry for interval 16 mt + li is
 // the A operand; every product is exact and the sums are FP32.
-__device__ void outputs_to_hist_f32(const TrackArgs& a, const float* hb, const int* iv, int n, int wave, int lane,
-                                    f32x4 (&h)[2][kRegMT])
+template <int NW>
+__device__ void outputs_to_hist_f32(const TrackArgs& a, const float* hb, const int* iv, int n, int jt0, int lane,
+                                    f32x4 (&h)[8 / NW][kRegMT])
 {
     const int li = lane & 15, lg = lane >> 4;
     const float* Wo = a.mlp + kHidden * kFeat + kHidden +
@@ -803,8 +876,8 @@ __device__ void outputs_to_hist_f32(const TrackArgs& a, const float* hb, const i
     const float* bo = Wo + (size_t)a.n_out * kHidden;
     constexpr int KS = kHidden / 4;
 #pragma unroll
-    for (int jl = 0; jl < 2; ++jl) {
-        const int jt = hist_tile(wave, blockIdx.x, jl);
+    for (int jl = 0; jl < 8 / NW; ++jl) {
+        const int jt = jt0 + 4 * jl;
         if (jt >= kMlpOutN / 16 || 16 * jt >= a.n_out) continue;
         const int c = 16 * jt + li;
         const bool used = c < a.n_out;
@@ -846,10 +919,17 @@ constexpr size_t row_tile_bytes()
     else return (size_t)NT * Net<E>::KP * sizeof(E);
 }
 
-template <class E>
-__device__ void track_event_mma(const TrackArgs& a, int e, char* smem)
+// NW waves: with four, wave w runs the hidden layers of its own 64 items and
+// two column tiles; with eight, tiles w and w + 8 of the chunk's sixteen and one
+// column tile, and the next chunk's features are on their way while a chunk
+// runs (no calibration).  Every item and every bin gets the same operations in
+// the same order.
+template <class E, int NW>
+__device__ void track_event_mma(const TrackArgs& a, int e, int part, char* smem)
 {
     constexpr bool kF32 = sizeof(E) == 4;
+    constexpr bool kWide = NW == 8;
+    constexpr int JL = 8 / NW;
     E* xa = reinterpret_cast<E*>(smem);            // [NT][KP] layer inputs (matrix-core network)
     float* hb = reinterpret_cast<float*>(smem);    // [NT][HPM] layer rows (FP32 network)
     int* iv = reinterpret_cast<int*>(smem + row_tile_bytes<E>());    // [NT] interval of each item
@@ -860,9 +940,10 @@ __device__ void track_event_mma(const TrackArgs& a, int e, char* smem)
 
     const int tid = threadIdx.x;
     const int lane = tid & 63, wave = tid >> 6;
-    f32x4 h[2][kRegMT];
+    const int jt0 = hist_tile<NW>(wave, blockIdx.x, part);
+    f32x4 h[JL][kRegMT];
 #pragma unroll
-    for (int jl = 0; jl < 2; ++jl)
+    for (int jl = 0; jl < JL; ++jl)
 #pragma unroll
         for (int mt = 0; mt < kRegMT; ++mt) h[jl][mt] = f32x4{0.f, 0.f, 0.f, 0.f};
 
@@ -880,54 +961,72 @@ __device__ void track_event_mma(const TrackArgs& a, int e, char* smem)
     // hidden layers of one item per thread, into hb (FP32) or xa; a wave
     // without a single kept item skips the network (its rows are never
     // accumulated, and it adds nothing to a calibration maximum)
-    auto network_hidden = [&](const float* g, bool valid) {
+    auto network_hidden = [&](const float* g, bool valid, int n) {
         const bool any = __ballot(valid) != 0;
         if constexpr (kF32) {
+            if (!kWide || tid < NT)
 #pragma unroll
-            for (int k = 0; k < kFeat; ++k) hb[tid * HPM + k] = valid ? g[k] : 0.f;
-            if (a.mlp_calib)
+                for (int k = 0; k < kFeat; ++k) hb[tid * HPM + k] = valid ? g[k] : 0.f;
+            if (!kWide && a.mlp_calib)
 #pragma unroll
                 for (int k = 0; k < kFeat; ++k) wave_amax(a.mlp_calib + calib_off(0) + k, valid ? g[k] : 0.f);
-            __builtin_amdgcn_wave_barrier();
-            if (any) hidden_layers_f32_mma(a, hb, iv, wave, lane);
+            if constexpr (kWide) {
+                __syncthreads();
+                if (16 * wave < n) hidden_layers_f32_mma<2, 128, 2, true>(a, hb, iv, 16 * wave, lane);
+            } else {
+                __builtin_amdgcn_wave_barrier();
+                if (any) hidden_layers_f32_mma<4, 16, 1, false>(a, hb, iv, 64 * wave, lane);
+            }
         } else {
             float z[kFeat];
 #pragma unroll
             for (int k = 0; k < kFeat; ++k) z[k] = valid ? g[k] : 0.f;
-            if (a.mlp_calib)
+            if (!kWide && a.mlp_calib)
 #pragma unroll
                 for (int k = 0; k < kFeat; ++k) wave_amax(a.mlp_calib + calib_off(0) + k, z[k]);
-            store_inputs<E>(a, xa, tid, z);
-            __builtin_amdgcn_wave_barrier();
-            if (any) hidden_layers_mma<E>(a, xa, iv, wave, lane);
+            if (!kWide || tid < NT) store_inputs<E>(a, xa, tid, z);
+            if constexpr (kWide) {
+                __syncthreads();
+                if (16 * wave < n) hidden_layers_mma<E, 2, 128, true>(a, xa, iv, 16 * wave, lane);
+            } else {
+                __builtin_amdgcn_wave_barrier();
+                if (any) hidden_layers_mma<E, 4, 16, false>(a, xa, iv, 64 * wave, lane);
+            }
         }
     };
     auto outputs = [&](int n) {
-        if constexpr (kF32) outputs_to_hist_f32(a, hb, iv, n, wave, lane, h);
-        else outputs_to_hist<E>(a, xa, iv, n, wave, lane, h);
+        if constexpr (kF32) outputs_to_hist_f32<NW>(a, hb, iv, n, jt0, lane, h);
+        else outputs_to_hist<E, NW>(a, xa, iv, n, jt0, lane, h);
     };
 
     if (status == 0) {
+        const bool item = !kWide || tid < NT;          // the threads that hold the chunk's items
+        float f[kFeat];
+        if (kWide && item && beg + tid < end) load_track(a, beg + tid, f);
         for (int64_t base = beg; base < end; base += NT) {
             const int64_t t = base + tid;
             int itv = -1, nb = -1;
             float g[kFeat];
 #pragma unroll
             for (int k = 0; k < kFeat; ++k) g[k] = 0.f;
-            if (t < end) bin_track(a, t, z_max, two, itv, nb, g, &dropped_any);
-            iv[tid] = itv;   // read by the hidden layers' calibration
-            network_hidden(g, itv >= 0);
-            nbv[tid] = nb;
-            __syncthreads();
+            if (item && t < end) {
+                if (!kWide) load_track(a, t, f);
+                bin_track(a, f, z_max, two, itv, nb, g, &dropped_any);
+                if (kWide && t + NT < end) load_track(a, t + NT, f);
+            }
             const int n_chunk = (int)((end - base) < NT ? (end - base) : NT);
+            if (item) iv[tid] = itv;   // read by the hidden layers' calibration
+            network_hidden(g, itv >= 0, n_chunk);
+            if (item) nbv[tid] = nb;
+            __syncthreads();
             outputs(n_chunk);
             if (two) {
                 // the chunk's boundary items, in item order, once more in the
                 // neighbour's frame (the barrier below also ends every wave's
                 // reads of xa and iv above)
-                const bool is_b = nbv[tid] >= 0;
+                const bool is_b = item && nbv[tid] >= 0;
                 const uint64_t m = __ballot(is_b);
-                if (lane == 0) wave_count[wave] = __popcll(m);
+                if (lane == 0 && (!kWide || wave < NT / 64)) wave_count[wave] = __popcll(m);
                 __syncthreads();
                 int off = 0, n_st = 0;
 #pragma unroll
@@ -942,7 +1041,7 @@ __device__ void track_event_mma(const TrackArgs& a, int e, char* smem)
                     float gs[kFeat];
 #pragma unroll
                     for (int k = 0; k < kFeat; ++k) gs[k] = 0.f;
-                    if (tid < n_st) {
+                    if (item && tid < n_st) {
                         const int src = st[tid];
                         inb = nbv[src];
                         float fs[kFeat];
@@ -951,8 +1050,8 @@ __device__ void track_event_mma(const TrackArgs& a, int e, char* smem)
                         features(a, fs, (double)fs[0], inb, gs);
                     }
                     __syncthreads();    // every read of nbv / st above is done
-                    iv[tid] = inb;
-                    network_hidden(gs, tid < n_st);
+                    if (item) iv[tid] = inb;
+                    network_hidden(gs, item && tid < n_st, n_st);
                     __syncthreads();
                     outputs(n_st);
                 }
@@ -966,14 +1065,15 @@ __device__ void track_event_mma(const TrackArgs& a, int e, char* smem)
     const int n_bins = a.n_out * a.n_intervals;
     const int U = n_bins / a.unit_bins;
     float* x0 = a.x0 + (int64_t)e * U * a.r0 + kGuard;
+    const int row = U == 1 ? a.n_out : a.r0;      // from one interval's bins to the next one's
     // the store addresses are formed here, not held in registers (or spilled)
     // through the event
     int lo = lane;
     asm volatile("" : "+v"(lo));
     const int li = lo & 15, lg = lo >> 4;
 #pragma unroll
-    for (int jl = 0; jl < 2; ++jl) {
-        const int jt = hist_tile(wave, blockIdx.x, jl);
+    for (int jl = 0; jl < JL; ++jl) {
+        const int jt = jt0 + 4 * jl;
         const int c = 16 * jt + li;
         if (jt >= kMlpOutN / 16 || c >= a.n_out) continue;
 #pragma unroll
@@ -982,21 +1082,22 @@ __device__ void track_event_mma(const TrackArgs& a, int e, char* smem)
             for (int v = 0; v < 4; ++v) {
                 const int iw = 16 * mt + 4 * lg + v;
                 if (iw >= a.n_intervals) continue;
-                const int bb = iw * a.n_out + c;
-                const int u = bb / a.unit_bins;
-                x0[(int64_t)u * a.r0 + (bb - u * a.unit_bins)] = a.s_in * h[jl][mt][v];
+                x0[iw * row + c] = a.s_in * h[jl][mt][v];
             }
     }
-    if (tid == 0) a.flags[e] = status | (dropped_any ? PVF_EV_TRACKS_DROPPED : 0);
+    if (tid == 0 && part <= 0) a.flags[e] = status | (dropped_any ? PVF_EV_TRACKS_DROPPED : 0);
     __syncthreads();   // the block's LDS is reused by its next event
 }
 
 // One block per event (queued == 0, grid = events), or the work-queue form
 // of track_stage_queue (queued == 1) when the events outnumber the blocks
-// that fit on the device at once.
-template <class E>
-__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void track_stage_mma(TrackArgs a, int n_events,
-                                                                                         int queued)
+// that fit on the device at once; split (NW = 8, not queued): two blocks per
+// event, each with half of the column tiles and all of the hidden layers.
+// NW = 4: four blocks share a CU, for batches that fill the device; NW = 8: the
+// work of an event spread over twice the waves, for batches that do not.
+template <class E, int NW>
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NW == 4 ? 4 : 2))) void track_stage_mma(
+    TrackArgs a, int n_events, int queued, int split)
 {
     extern __shared__ __attribute__((aligned(16))) char smem_mma[];
     __shared__ int ticket;
@@ -1008,8 +1109,8 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void tr
             k = ticket;
             __syncthreads();
         }
-        if (k >= n_events) break;
-        track_event_mma<E>(a, queued ? a.order[k] : k, smem_mma);
+        if (k >= (split ? 2 * n_events : n_events)) break;
+        track_event_mma<E, NW>(a, queued ? a.order[k] : (split ? k >> 1 : k), split ? k & 1 : -1, smem_mma);
         if (!queued) break;
     }
 }
@@ -1084,6 +1185,13 @@ static size_t track_mma_lds_bytes()
     return row_tile_bytes<E>() + 3 * NT * sizeof(int);
 }
 
+// Batches that leave compute units idle: up to 384 events eight waves an event,
+// up to 128 two blocks of them.  One event 36.5 us with the four-wave form in
+// FP32, 27 with eight waves, 21 with two blocks of eight (BF16 18, 15, 13); 333
+// heavy-tailed FP32 events (the largest of 1500 tracks) 253 and 193; at 500
+// FP32 events the four-wave form's 64 us beat 70.
+constexpr int kWideEvents = 384, kSplitEvents = 128;
+
 template <class E>
 hipError_t launch_track_typed(const TrackArgs& a, int n_events, int persistent_blocks, hipStream_t s)
 {
@@ -1098,8 +1206,13 @@ hipError_t launch_track_typed(const TrackArgs& a, int n_events, int persistent_b
                 const hipError_t err = hipGetLastError();
                 if (err != hipSuccess) return err;
             }
-            hipLaunchKernelGGL(track_stage_mma<E>, dim3(queued ? persistent_blocks : n_events), dim3(NT),
-                               track_mma_lds_bytes<E>(), s, a, n_events, queued);
+            const int split = n_events <= kSplitEvents;
+            if (!a.mlp_calib && n_events <= kWideEvents)
+                hipLaunchKernelGGL((track_stage_mma<E, 8>), dim3(n_events * (1 + split)), dim3(512), track_mma_lds_bytes<E>(), s, a,
+                                   n_events, 0, split);
+            else
+                hipLaunchKernelGGL((track_stage_mma<E, 4>), dim3(queued ? persistent_blocks : n_events), dim3(NT),
+                                   track_mma_lds_bytes<E>(), s, a, n_events, queued, 0);
             return hipGetLastError();
         }
     }
@@ -1145,19 +1258,19 @@ int track_queue_blocks(int dtype, int n_intervals, int n_out, int cu_count)
     hipError_t err = hipErrorInvalidValue;
     switch (dtype) {
     case PVF_FP32:
-        err = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, track_stage_mma<float>, NT,
+        err = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, track_stage_mma<float, 4>, NT,
                                                            track_mma_lds_bytes<float>());
         break;
     case PVF_BF16:
-        err = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, track_stage_mma<__bf16>, NT,
+        err = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, track_stage_mma<__bf16, 4>, NT,
                                                            track_mma_lds_bytes<__bf16>());
         break;
     case PVF_FP16:
-        err = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, track_stage_mma<_Float16>, NT,
+        err = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, track_stage_mma<_Float16, 4>, NT,
                                                            track_mma_lds_bytes<_Float16>());
         break;
     case PVF_FP8_E4M3:
-        err = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, track_stage_mma<uint8_t>, NT,
+        err = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, track_stage_mma<uint8_t, 4>, NT,
                                                            track_mma_lds_bytes<uint8_t>());
         break;
     default: break;
@@ -1168,7 +1281,7 @@ int track_queue_blocks(int dtype, int n_intervals, int n_out, int cu_count)
 std::string track_kernel_name(int dtype, bool persistent, int n_intervals, int n_out)
 {
     static const char* const kType[] = {"float", "__bf16", "_Float16", "unsigned char"};
-    if (track_mma_ok(n_intervals, n_out)) return std::string("track_stage_mma<") + kType[dtype] + ">";
+    if (track_mma_ok(n_intervals, n_out)) return std::string("track_stage_mma<") + kType[dtype] + ", 4>";
     return std::string(persistent ? "track_stage_queue<" : "track_stage<") + kType[dtype] + ">";
 }
 

@@ -57,3 +57,27 @@ def test_small_batch_tiles_interval_layout(dtype):
     shape = NetShape(n_levels=3)
     amax = fp8_calibration(32, 5, shape) if dtype == "fp8_e4m3" else None
     check(make_engine(12, fp8_amax=amax, shape=shape, compute_dtype=dtype, unet_layout="interval"), 12, [1, 2, 12])
+
+
+@pytest.mark.parametrize("dtype", ["fp32", "bf16", "fp16", "fp8_e4m3"])
+@pytest.mark.parametrize("boundary", [0.0, 2.5])
+def test_track_and_peak_forms_give_the_same_bits(dtype, boundary):
+    """Few events spread each event over more waves (track stage: 1 to 128, to
+    384, more; peaks: to 256, more).  Heavy-tailed events of one to six chunks,
+    the smallest of 5 tracks, without and with boundary tracks, at another half
+    window than the default's."""
+    torch_cuda()
+    most = 390
+    batch = make_events(most, seed=17, mix="lognormal")
+    eng = engine_for(most, dtype, boundary_mm=boundary, half_window=5 if boundary else 3)
+    full = run(eng, batch)
+    for n in (1, 128, 129, 257, 384):
+        print(f"[gpu-batch-tiles] {dtype} {n} events, boundary {boundary}", flush=True)
+        part = run(eng, batch.subset(range(n)))
+        for k in ("prob", "status", "n_vertices"):
+            assert np.array_equal(part[k], full[k][:n]), (n, k)
+        for e in range(n):
+            v = int(full["n_vertices"][e])
+            for k in ("z", "integral", "bin", "peak_prob"):
+                assert np.array_equal(part[k][e, :v], full[k][e, :v]), (n, e, k)
+    eng.close()
