@@ -271,19 +271,33 @@ class Engine:
         v.d_bin = out.bin.data_ptr() if out.bin is not None else None
         return tr, v
 
+    def _after_current(self, s):
+        """Stream `s` waits for the current stream's work, so that inputs
+        written there are visible.  Without a wait where there is nothing to
+        wait for: on the same stream, or when the current stream has no work
+        left (the wait costs the caller 36 us of the 92 us of a one-event
+        call, the query 1 us).  A capturing stream is not queried: its wait
+        becomes part of the capture."""
+        t = self._torch
+        cur = t.cuda.current_stream(self.device)
+        if cur == s:
+            return
+        if self.device.index == t.cuda.current_device() and not t.cuda.is_current_stream_capturing() and cur.query():
+            return
+        s.wait_stream(cur)
+
     def execute(self, feat, offsets, out: Outputs | None = None, stream=None) -> Outputs:
         """Enqueue one batch on the engine's stream (or `stream`); no sync.
 
         The engine's stream first waits for the current stream, so inputs
         written there are visible; call synchronize() (or make the current
         stream wait) before reading the outputs."""
-        t = self._torch
         n_events = offsets.shape[0] - 1
         if out is None:
             out = self.alloc_outputs(n_events)
         tr, v = self._views(feat, offsets, out)
         s = stream if stream is not None else self.stream
-        s.wait_stream(t.cuda.current_stream(self.device))
+        self._after_current(s)
         for x in (feat, offsets, out.n_vertices, out.z, out.peak_prob, out.integral, out.status, out.prob,
                   out.bin):
             if x is not None:
@@ -300,12 +314,11 @@ class Engine:
         the library's fixed per-device scratch (no allocation in the call).
         Same stream ordering as execute(); raises PvfError on a batch too
         large for the scratch (PVF_ERR_SCRATCH_TOO_SMALL)."""
-        t = self._torch
         n_events = offsets.shape[0] - 1
         if out is None:
             out = self.alloc_outputs(n_events)
         tr, v = self._views(feat, offsets, out)
-        self.stream.wait_stream(t.cuda.current_stream(self.device))
+        self._after_current(self.stream)
         for x in (feat, offsets, out.n_vertices, out.z, out.peak_prob, out.integral, out.status, out.prob,
                   out.bin):
             if x is not None:
@@ -343,11 +356,10 @@ class Engine:
 
     def autotune(self, feat, offsets, out: Outputs | None = None, reps: int = 2) -> list:
         """Time every variant on this batch and keep the fastest per launch."""
-        t = self._torch
         if out is None:
             out = self.alloc_outputs(offsets.shape[0] - 1)
         tr, v = self._views(feat, offsets, out)
-        self.stream.wait_stream(t.cuda.current_stream(self.device))
+        self._after_current(self.stream)
         _check("pvf_autotune", self.lib.pvf_autotune(self.handle, C.byref(tr), C.byref(v), reps))
         return self.variants()
 
@@ -359,7 +371,7 @@ class Engine:
         out = self.alloc_outputs(offsets.shape[0] - 1)
         amax = t.empty(n, dtype=t.float32, device=self.device)
         tr, v = self._views(feat, offsets, out)
-        self.stream.wait_stream(t.cuda.current_stream(self.device))
+        self._after_current(self.stream)
         _check("pvf_calibrate", self.lib.pvf_calibrate(self.handle, C.byref(tr), C.byref(v),
                                                        C.c_void_p(amax.data_ptr()), n))
         self.stream.synchronize()
@@ -377,8 +389,7 @@ class Engine:
 
     def graph_launch(self):
         """Replay the captured graph on the engine's stream (after the current stream's work)."""
-        t = self._torch
-        self.stream.wait_stream(t.cuda.current_stream(self.device))
+        self._after_current(self.stream)
         _check("pvf_graph_launch", self.lib.pvf_graph_launch(self.handle))
 
     def profile(self, on: bool = True):
