@@ -201,15 +201,17 @@ pvf_status pvf_execute(pvf_engine *eng, const pvf_tracks *tracks, const pvf_vert
 pvf_status pvf_execute_on(pvf_engine *eng, const pvf_tracks *tracks, const pvf_vertices *out,
                           void *stream);
 
-/* Bytes of the library's fixed per-device scratch (64 MiB). */
+/* Bytes of a scratch area (64 MiB), and the areas that the library holds on
+ * each device. */
 #define PVF_SCRATCH_BYTES (64u << 20)
+#define PVF_SCRATCH_AREAS 4
 
 /* For callers that cannot allocate device memory (code under HIP graph
  * capture, tight serving loops, harnesses that forbid allocation): the same
  * path and kernels as pvf_execute, with the same results bit for bit, but
  * every per-batch buffer (histogram rows, activations, the probability rows
  * when d_prob_hist is NULL, flags, the track work queue) lives in a fixed
- * scratch array that the library holds on each device until the process
+ * scratch area that the library holds on each device until the process
  * ends, instead of in the engine's arena; of the arena, the call reads only
  * the weights.  Calls nothing that allocates.
  * Limit: the batch's per-batch buffers must fit PVF_SCRATCH_BYTES (about
@@ -217,11 +219,13 @@ pvf_status pvf_execute_on(pvf_engine *eng, const pvf_tracks *tracks, const pvf_v
  * 1.8 MiB in FP8: 8, 17 and 35 events); a larger batch returns
  * PVF_ERR_SCRATCH_TOO_SMALL and enqueues nothing.  The other checks are
  * those of pvf_execute.
- * Sharing: every engine on a device uses that device's one scratch, and it
- * keeps the last call's contents (each call clears what it needs zeroed, on
- * the stream, before its kernels).  Calls that overlap in time on one
- * device race and corrupt each other's results: order them on one stream,
- * or with events.  pvf_debug_tensor views only pvf_execute calls.
+ * Sharing: an engine takes the area with the fewest live engines on its
+ * device at initialisation and gives it back in pvf_destroy (after its work is
+ * done), so up to PVF_SCRATCH_AREAS engines have one each; further engines
+ * share.  An area keeps the last call's contents (each call clears what it
+ * needs zeroed, on the stream, before its kernels).  Calls on one area that
+ * overlap in time race and corrupt each other's results: order them on one
+ * stream, or with events.  pvf_debug_tensor views only pvf_execute calls.
  * PVF_ERR_DEVICE if the scratch's device address could not be obtained. */
 pvf_status pvf_execute_scratch(pvf_engine *eng, const pvf_tracks *tracks, const pvf_vertices *out);
 

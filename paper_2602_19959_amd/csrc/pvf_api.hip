@@ -386,7 +386,8 @@ struct pvf_engine {
     float leaky = 0.f, s_in = 0.f, head_b = 0.f;
     float shift[kFeat] = {}, scale[kFeat] = {};
     char* arena = nullptr;
-    char* scratch = nullptr;             // the library's scratch on this engine's device
+    char* scratch = nullptr;             // this engine's scratch area on its device
+    int device = 0;
     hipStream_t stream = nullptr;
     std::vector<std::string> names;      // one per launch of pvf_execute
     std::vector<std::string> kernels;    // kernel instance of each launch
@@ -1050,7 +1051,7 @@ static pvf_status init_impl(const pvf_spec* spec, const void* blob, size_t blob_
     }
     e->track_blocks = track_queue_blocks(e->spec.compute_dtype, e->spec.n_bins / e->spec.bins_per_interval,
                                          e->spec.bins_per_interval, e->cu_count);
-    e->scratch = scratch_base(dev);      // set-up of pvf_execute_scratch, once per device
+    e->device = dev;
     build_names(e);
 
     std::vector<float> packed;
@@ -1102,6 +1103,7 @@ static pvf_status init_impl(const pvf_spec* spec, const void* blob, size_t blob_
         delete e;
         return PVF_ERR_DEVICE;
     }
+    e->scratch = scratch_take(dev);      // for pvf_execute_scratch, until pvf_destroy
     *out = e;
     return PVF_OK;
 }
@@ -1192,6 +1194,7 @@ pvf_status pvf_destroy(pvf_engine* eng)
     if (eng->graph_exec) (void)hipGraphExecDestroy(eng->graph_exec);
     if (eng->graph) (void)hipGraphDestroy(eng->graph);
     for (hipEvent_t ev : eng->events) (void)hipEventDestroy(ev);
+    scratch_give_back(eng->device, eng->scratch);
     delete eng;
     return PVF_OK;
 }

@@ -342,8 +342,9 @@ inline int act_bytes(int dtype) { return dtype == PVF_FP32 ? 4 : (dtype == PVF_F
 
 hipError_t launch_peaks(const PeakArgs& a, int n_events, hipStream_t s);
 
-// The library's fixed per-device scratch (pvf_execute_scratch).
+// The library's fixed per-device scratch areas (pvf_execute_scratch).
 constexpr size_t kScratchBytes = PVF_SCRATCH_BYTES;
+constexpr int kScratchSlots = PVF_SCRATCH_AREAS;
 constexpr int kMaxGuardRegions = 1 + 4 * kMaxLevels;
 struct GuardRegion {
     char* base;          // first row of the region's first sequence
@@ -355,9 +356,11 @@ struct GuardZeroArgs {
     int n;               // regions
     int64_t n_seq;       // sequences per region
 };
-// Device address of the scratch on `device` (which must be current): looked
-// up once per device and cached; nullptr if the lookup failed.
-char* scratch_base(int device);
+// A scratch area of `device` (which must be current) for one engine, the one
+// with the fewest engines on it, and its return; nullptr if the device address
+// could not be obtained.  Any thread.
+char* scratch_take(int device);
+void scratch_give_back(int device, const char* area);
 // Clear the kGuard rows at both ends of every sequence of every region.
 hipError_t launch_zero_guard_rows(const GuardZeroArgs& a, hipStream_t s);
 hipError_t launch_gather(const GatherArgs& a, hipStream_t s);

@@ -1,5 +1,11 @@
-// The library's fixed per-device working area, for pvf_execute_scratch
+// The library's fixed per-device working areas, for pvf_execute_scratch
 // (callers that cannot allocate device memory).
+//
+// There are kScratchSlots of them on a device.  An engine takes the one with
+// the fewest live engines when it is made and gives it back when it is
+// destroyed, so calls of up to kScratchSlots engines may overlap on a device
+// (three one-event engines in turn then run side by side, where one area would
+// have them corrupt each other or wait).
 //
 // `scratch` is a file-scope device array: every GPU the library runs on holds
 // its own copy, at its own address, until the process ends.  Host code never
@@ -21,7 +27,7 @@
 
 namespace pvf {
 
-static __device__ __align__(256) unsigned char scratch[kScratchBytes];
+static __device__ __align__(256) unsigned char scratch[kScratchSlots * kScratchBytes];
 
 namespace {
 
@@ -29,6 +35,7 @@ constexpr int kMaxDevices = 64;
 std::mutex g_lock;
 bool g_resolved[kMaxDevices] = {};
 char* g_ptr[kMaxDevices] = {};
+int g_users[kMaxDevices][kScratchSlots] = {};   // live engines on each area
 
 // Zero the first and last kGuard rows of every sequence of region blockIdx.y;
 // 4-byte stores (row sizes are multiples of 4 bytes).
@@ -49,7 +56,7 @@ __global__ __launch_bounds__(256) void zero_guard_rows(GuardZeroArgs a)
 
 }  // namespace
 
-char* scratch_base(int device)
+char* scratch_take(int device)
 {
     if (device < 0 || device >= kMaxDevices) return nullptr;
     std::lock_guard<std::mutex> lock(g_lock);
@@ -63,7 +70,18 @@ char* scratch_base(int device)
         g_ptr[device] = static_cast<char*>(p);
         g_resolved[device] = true;
     }
-    return g_ptr[device];
+    int slot = 0;
+    for (int k = 1; k < kScratchSlots; ++k)
+        if (g_users[device][k] < g_users[device][slot]) slot = k;
+    ++g_users[device][slot];
+    return g_ptr[device] + (size_t)slot * kScratchBytes;
+}
+
+void scratch_give_back(int device, const char* area)
+{
+    if (device < 0 || device >= kMaxDevices || !area) return;
+    std::lock_guard<std::mutex> lock(g_lock);
+    --g_users[device][(size_t)(area - g_ptr[device]) / kScratchBytes];
 }
 
 hipError_t launch_zero_guard_rows(const GuardZeroArgs& a, hipStream_t s)
