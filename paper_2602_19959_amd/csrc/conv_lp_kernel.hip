@@ -960,6 +960,161 @@ void conv_mfma_lp_dec0d(ConvArgs c1, ConvArgs c2)
     }
 }
 
+// Two 5-tap convolutions with 64 output channels each and the max-pool in one
+// launch (enc1 of the 32-channel network): the 64-channel tensor between them
+// stays in LDS.  Apart they wait on HBM, which carries that tensor twice (half
+// the bytes of the two launches): 1000 events in BF16 250 us, fused 227; now
+// the three loads a block waits for, and the matrix cores.  A block of 4 waves
+// owns BO = 240 output rows from m0:
+//   phase 1 computes c1's outputs for the BA = 256 rows from m0 - 2 (the tile
+//     and its halo), rounds them as the stored tensor is, zeroes rows that are
+//     guard rows or outside the batch, and keeps them as two swizzled
+//     32-channel tiles in the halo's place;
+//   phase 2 runs c2 on those tiles, one 32-channel stage of weights at a time.
+// Stages load straight into LDS, single-buffered: 52 KB, so three blocks to a
+// CU cover each other's loads.  Fragments, k order and epilogues are the
+// separate launches', hence the same bits.
+template <class T>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3)))
+void conv_mfma_lp_pair(ConvArgs c1, ConvArgs c2)
+{
+    using V = typename Lp<T>::vec8;
+    constexpr int NW = 4, N = 64;
+    constexpr int BA = NW * 64;                  // phase-1 rows per block
+    constexpr int BO = BA - 16;                  // output rows per block
+    constexpr int KC = 32, NCH = 4;              // 32-channel stages, 64-byte rows
+    constexpr int ROWB = KC * (int)sizeof(T);
+    constexpr int XI = (BA + kTaps - 1 + 15) / 16;         // 1 KB loads of the input halo
+    constexpr int WI = kTaps * N / 16;                     // and of a weight stage (rows tap * 64 + column)
+    constexpr int TILE = BA * ROWB;                        // one 32-channel tile of c1's output
+    static_assert(XI * 16 * ROWB <= 2 * TILE, "the halo lies where the tiles go");
+    static_assert(BA * (N + 8) * (int)sizeof(T) <= 2 * TILE + WI * 16 * ROWB, "epilogue tile");
+    __shared__ __attribute__((aligned(16))) char smem[2 * TILE + WI * 16 * ROWB];
+    T* const xs = reinterpret_cast<T*>(smem);
+    T* const ws = reinterpret_cast<T*>(smem + 2 * TILE);
+
+    const int tid = threadIdx.x;
+    const int lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int li = lane & 15, lg = lane >> 4;
+    const int m_tiles = (int)((c2.m_rows + BO - 1) / BO);
+    const int xcd = (int)(blockIdx.x % kXcds), slot = (int)(blockIdx.x / kXcds);
+    const int m_tile = slot * kXcds + xcd;
+    if (m_tile >= m_tiles) return;
+    const int64_t m0 = (int64_t)m_tile * BO;
+    const int64_t a0 = m0 - 2;                   // first phase-1 row
+
+    // Wave-wide load j fills LDS rows 16 j .. 16 j + 15; lane L fills slot L % 4
+    // of row L / 4 with the chunk the swizzle puts there.  Halo rows outside the
+    // batch are clamped (they only feed zeroed or discarded rows).
+    const int lrow = lane >> 2, lpos = lane & 3;
+    const char* xbase = reinterpret_cast<const char*>(static_cast<const T*>(c1.in) + (a0 - 2) * c1.ld_in);
+    auto issue_x = [&](int c0) __attribute__((always_inline)) {
+#pragma unroll
+        for (int t = 0; t < (XI + NW - 1) / NW; ++t) {
+            const int j = wave + t * NW;
+            if ((t + 1) * NW > XI && j >= XI) continue;
+            const int row = 16 * j + lrow;
+            int64_t g = a0 - 2 + row;
+            g = g < 0 ? 0 : (g >= c1.m_rows ? c1.m_rows - 1 : g);
+            const unsigned off = (unsigned)(((g - (a0 - 2)) * c1.ld_in + c0 + 8 * (lpos ^ swz<NCH>(row))) * (int64_t)sizeof(T));
+            __builtin_amdgcn_global_load_lds((const void*)(xbase + off),
+                                             (__attribute__((address_space(3))) void*)(smem + j * 16 * ROWB), 16, 0, 0);
+        }
+    };
+    auto issue_w = [&](const ConvArgs& a, int c0) __attribute__((always_inline)) {
+#pragma unroll
+        for (int t = 0; t < WI / NW; ++t) {
+            const int j = wave + t * NW;
+            const int row = 16 * j + lrow, tap = row / N, n = row % N;
+            const unsigned off = (unsigned)((n * (kTaps * a.cin) + tap * a.cin + c0 + 8 * (lpos ^ swz<NCH>(row))) * (int)sizeof(T));
+            __builtin_amdgcn_global_load_lds((const void*)(static_cast<const char*>(a.w) + off),
+                                             (__attribute__((address_space(3))) void*)(smem + 2 * TILE + j * 16 * ROWB),
+                                             16, 0, 0);
+        }
+    };
+    static_assert(WI % NW == 0, "equal shares of a weight stage");
+
+    f32x4 acc[4][4];
+    auto clear = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    };
+    // one 32-channel stage; x: the tile whose row r is one tap-0 row of output row r
+    auto stage = [&](const T* x) __attribute__((always_inline)) {
+#pragma unroll
+        for (int tap = 0; tap < kTaps; ++tap) {
+            V av[4], bv[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) av[i] = *reinterpret_cast<const V*>(x + lds_at<NCH>(wave * 64 + i * 16 + li + tap, lg));
+#pragma unroll
+            for (int j = 0; j < 4; ++j) bv[j] = *reinterpret_cast<const V*>(ws + lds_at<NCH>(tap * N + j * 16 + li, lg));
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) acc[i][j] = Lp<T>::mfma(bv[j], av[i], acc[i][j]);
+        }
+    };
+
+    // ---- phase 1: c1 over rows a0 .. a0 + BA - 1
+    clear();
+    issue_x(0);
+    issue_w(c1, 0);
+    for (int c0 = 0; c0 < c1.cin; c0 += KC) {
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();
+        stage(xs);
+        __syncthreads();   // every wave is past its reads of the stage
+        if (c0 + KC < c1.cin) {
+            issue_x(c0 + KC);
+            issue_w(c1, c0 + KC);
+        }
+    }
+    issue_w(c2, 0);
+    // c1's epilogue into the tiles: row r is row a0 + r
+    {
+        const RowMap rmap(a0 < 0 ? 0 : a0, c1.r_in);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int r = wave * 64 + i * 16 + li;
+            const int64_t g = a0 + r;
+            bool keep = g >= 0 && g < c1.m_rows;
+            if (keep) {
+                int64_t e;
+                int loc;
+                rmap.at((int)(g - (a0 < 0 ? 0 : a0)), e, loc);
+                keep = loc >= kGuard && loc < c1.r_in - kGuard;
+            }
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const int col = j * 16 + 4 * lg;
+                T y[4];
+#pragma unroll
+                for (int v = 0; v < 4; ++v) y[v] = keep ? (T)lrelu(acc[i][j][v] + c1.bias[col + v], c1.slope) : (T)0.f;
+                *reinterpret_cast<uint2*>(xs + (col / KC) * (BA * KC) + lds_at<NCH>(r, col % KC / 8) + (col % 8)) =
+                    *reinterpret_cast<const uint2*>(y);
+            }
+        }
+    }
+    // ---- phase 2: c2 on the tiles (rows BA .. BA + 3 of a tile are whatever
+    // follows it in LDS: they only feed output rows from BO on, which are not stored)
+    clear();
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    stage(xs);
+    __syncthreads();
+    issue_w(c2, KC);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    stage(xs + BA * KC);
+    __syncthreads();       // the epilogue's tile takes the buffers
+    const int64_t end = m0 + BO;
+    if (end < c2.m_rows) c2.m_rows = (int)end;   // rows from BO on are the next block's
+    lp_epilogue<T, NW * 64, BA, N, NW, 4, 4, EPI_POOL>(acc, c2, smem, m0, 0, tid);
+}
+
 // enc0.c2 (32 channels in and out) with the first convolution computed in
 // its staging, the weight tile loaded straight into LDS: no staging
 // registers, the first convolution's weights and biases in LDS (one copy per
@@ -1161,6 +1316,7 @@ constexpr Variant kVariants[] = {
     {2, 4, 2, 2, 32, 2},   // 39: 64 x 128, double-buffered (512 threads)
     {1, 2, 2, 2, 32, 2},   // 40: 32 x 64, double-buffered (128 threads)
     {2, 2, 2, 2, 32, 2},   // 41: 64 x 64, double-buffered
+    {4, 1, 4, 4, 32, 8},   // 42: enc1.c2 of the 32-channel network with enc1.c1 (conv_mfma_lp_pair, 240 rows); elsewhere 28's tile
 };
 constexpr int kNumVariants = sizeof(kVariants) / sizeof(kVariants[0]);
 
@@ -1258,6 +1414,7 @@ hipError_t dispatch(int v, const ConvArgs& a, hipStream_t s)
         case 33: return run<T, 2, 1, 4, 2, 32, 0, TAPS, EPI>(a, s);
         case 34: return run<T, 4, 1, 4, 2, 32, 0, TAPS, EPI>(a, s);
         case 35: return run<T, 8, 1, 4, 2, 32, 0, TAPS, EPI>(a, s);
+        case 42: return run<T, 4, 1, 4, 4, 32, 4, TAPS, EPI>(a, s);   // not fused
         default: return hipErrorInvalidValue;
         }
     }
@@ -1288,6 +1445,7 @@ bool lp_variant_ok(int v, int n, int cin, int taps, Epi epi)
     if (v < 0 || v >= kNumVariants) return false;
     const Variant& x = kVariants[v];
     if (x.pf == 3 || x.pf == 5) return epi == EPI_HEAD && n == 32 && cin == 32 && taps == kTaps;   // dec0 fused: 32-channel head
+    if (x.pf == 8) return epi == EPI_POOL && n == 64 && cin == 64 && taps == kTaps;   // two 64-channel convs
     if (x.pf == 6) return epi == EPI_POOL && n == 32 && cin == 32 && taps == kTaps;   // enc0.c2 of 32 channels
     const int bn = x.wn * x.tnw * 16;
     if (cin % x.kc != 0) return false;
@@ -1340,6 +1498,16 @@ int lp_default_up_variant(int n, int cin)
 int lp_batch_variant(int full, int n, int cin, Epi epi, int m_rows)
 {
     constexpr int kCus = 256;
+    if (lp_pair_ok(full)) {
+        // enc1.c2 with enc1.c1: three blocks of 240 rows to a compute unit, so
+        // rounds of 768 blocks, taken when there are more than two or three quarters
+        // of the slots of one or two are filled.  Both launches' time, fused and apart: 48
+        // events (0.5 rounds) 17 us and 14; 90 (0.98) 22 and 27; 97 (1.05) 31
+        // and 27; 128 (1.4) 35 and 33; 160 (1.7) 37 and 44; 250 (2.7) 53 and 64
+        const int64_t blocks = tile_blocks(m_rows, n, 240, 64), round = 3 * kCus;
+        if (blocks > 2 * round || 4 * blocks >= 3 * round * ((blocks + round - 1) / round)) return full;
+        full = 28;
+    }
     int v = full;
     if (lp_dec0_ok(full)) {
         // dec0.c1 and the head in one launch: 240 rows a block while that fills at most one round (one event 7.8 us, 8.6 with 496)
@@ -1396,9 +1564,31 @@ hipError_t launch_conv_lp_dec0(int dtype, const ConvArgs& c1, const ConvArgs& c2
     return hipGetLastError();
 }
 
+bool lp_pair_ok(int v) { return v >= 0 && v < kNumVariants && kVariants[v].pf == 8; }
+
+hipError_t launch_conv_lp_pair(int dtype, const ConvArgs& c1, const ConvArgs& c2, int v, hipStream_t s)
+{
+    if (!lp_pair_ok(v) || c1.cin % 32 != 0 || c1.cin <= 0 || c1.n != 64 || c2.cin != 64 || c2.n != 64 ||
+        c1.m_rows != c2.m_rows || c1.r_in != c2.r_in || c2.m_rows <= 0 || !c2.out || !c2.pool_out)
+        return hipErrorInvalidValue;
+    const int bo = kVariants[v].wm * 64 - 16;
+    const unsigned m_tiles = (unsigned)((c2.m_rows + bo - 1) / bo);
+    dim3 grid((m_tiles + kXcds - 1) / kXcds * kXcds);
+    if (dtype == PVF_BF16) hipLaunchKernelGGL((conv_mfma_lp_pair<__bf16>), grid, dim3(256), 0, s, c1, c2);
+    else if (dtype == PVF_FP16) hipLaunchKernelGGL((conv_mfma_lp_pair<_Float16>), grid, dim3(256), 0, s, c1, c2);
+    else return hipErrorInvalidValue;
+    return hipGetLastError();
+}
+
+std::string lp_pair_kernel_name(int dtype)
+{
+    return std::string("conv_mfma_lp_pair<") + (dtype == PVF_BF16 ? "__bf16>" : "_Float16>");
+}
+
 std::string lp_kernel_name(int dtype, int v, int taps, Epi epi)
 {
     const Variant& x = kVariants[v];
+    if (x.pf == 8) return lp_kernel_name(dtype, 28, taps, epi);   // not fused
     if (x.pf == 6)   // not fused: the register-staged tile of the same shape runs
         return std::string("conv_mfma_lp<") + (dtype == PVF_BF16 ? "__bf16" : "_Float16") + ", " +
                std::to_string(x.wm) + ", 1, " + std::to_string(x.tmw) + ", 2, 32, 0, " + std::to_string(taps) + ", " +

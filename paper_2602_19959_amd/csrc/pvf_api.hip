@@ -402,6 +402,7 @@ struct pvf_engine {
         size_t fold = 0;              // FP8 stored outputs: [n] s_n / a_out, then [n] bias / a_out
         bool first = false;           // enc0.c2: may compute the first convolution (the launch before it) itself
         bool up = false;              // dec(l+1).c2: may run the transposed conv (the launch after it) in its epilogue
+        bool pair = false;            // 16-bit enc(l).c2: may compute enc(l).c1 (the launch before it) in the same kernel
         bool dec0 = false;            // dec0.c2+head: may compute dec0.c1 (the launch before it) in the same kernel
     };
     std::vector<int> out_channels;       // channels of the tensor launch i stores (0: none)
@@ -465,6 +466,30 @@ bool fuses_dec0(const pvf_engine* e, int i, int v)
     return e->conv[i].dec0 && !e->calib_table && conv_dec0_ok(e->spec.compute_dtype, v);
 }
 bool fuses_dec0(const pvf_engine* e, int i) { return fuses_dec0(e, i, e->conv[i].variant); }
+
+// Whether launch i (an encoder conv2 with the max-pool) with tile variant v
+// computes the conv1 before it in the same kernel.  A conv1 whose own variant
+// the caller set, under a conv2 left at its default, runs as set.
+bool fuses_pair(const pvf_engine* e, int i, int v)
+{
+    const auto& c = e->conv[i];
+    return c.pair && !e->calib_table && lp_pair_ok(v) && (c.pinned || !e->conv[i - 1].pinned);
+}
+bool fuses_pair(const pvf_engine* e, int i) { return fuses_pair(e, i, e->conv[i].variant); }
+
+// Kernel names of an encoder level's two convs for conv2's current variant.
+void name_pair(pvf_engine* e)
+{
+    const int dt = e->spec.compute_dtype;
+    for (size_t i = 1; i < e->conv.size(); ++i) {
+        const auto& c = e->conv[i];
+        if (!c.pair) continue;
+        const auto& p = e->conv[i - 1];
+        const bool f = fuses_pair(e, (int)i);
+        e->kernels[i] = f ? lp_pair_kernel_name(dt) : conv_kernel_name(dt, c.variant, c.cin, c.taps, c.epi);
+        e->kernels[i - 1] = f ? "conv (in " + e->names[i] + ")" : conv_kernel_name(dt, p.variant, p.cin, p.taps, p.epi);
+    }
+}
 
 // Kernel names of dec0.c1 and dec0.c2 + head for the head's current variant.
 void name_dec0(pvf_engine* e)
@@ -580,6 +605,16 @@ void build_names(pvf_engine* e)
         if (v >= 0) c.variant = v;
     }
     name_up(e);
+    // enc(l).c2 of 64 channels may compute enc(l).c1 (the launch before it) itself
+    if (act_bytes(e->spec.compute_dtype) == 2)
+        for (int l = 1; l < n - 1; ++l) {
+            const int p = find("enc" + std::to_string(l) + ".c2");
+            if (p < 1 || find("enc" + std::to_string(l) + ".c1") != p - 1) continue;
+            auto& c = e->conv[p];
+            c.pair = c.n == 64 && c.cin == 64 && e->conv[p - 1].n == 64;
+            if (c.pair) c.variant = 42;
+        }
+    name_pair(e);
     // dec0.c2 + head may compute dec0.c1 (the launch before it) itself
     {
         const int h = find("dec0.c2+head");
@@ -867,10 +902,18 @@ pvf_status enqueue(pvf_engine* eng, const pvf_tracks* tr, const pvf_vertices* ou
 
     for (int l = 0; l < n; ++l) {
         const Level& lv = P.lv[l];
+        ConvArgs c1{};
+        int pair_v = -1;              // >= 0: conv2's kernel computes conv1
         if (l > 0) {
             const Level& up = P.lv[l - 1];
-            conv(conv_args(eng, W.enc[l][0], act(P.pool[l]), up.C, lv.R, EU, act(P.a[l]), lv.C), kTaps, EPI_STORE,
-                 l, lv.C, 0);
+            c1 = conv_args(eng, W.enc[l][0], act(P.pool[l]), up.C, lv.R, EU, act(P.a[l]), lv.C);
+            const int v = tile(eng, li + 1, c1.m_rows);
+            if (fuses_pair(eng, li + 1, v)) {
+                pair_v = v;
+                check(hipSuccess);    // computed inside conv2's launch
+            } else {
+                conv(c1, kTaps, EPI_STORE, l, lv.C, 0);
+            }
         }
         if (l < n - 1) {
             ConvArgs a = conv_args(eng, W.enc[l][1], act(P.a[l]), lv.C, lv.R, EU, act(P.cat[l]), 2 * lv.C);
@@ -883,7 +926,8 @@ pvf_status enqueue(pvf_engine* eng, const pvf_tracks* tr, const pvf_vertices* ou
                 a.first_b = wbase + W.first_b;
                 a.first_inv_scale = scales ? scales + eng->outinv_off[first_li] : nullptr;
             }
-            conv(a, kTaps, EPI_POOL, l, 2 * lv.C, 0);
+            if (pair_v >= 0) check(launch_conv_lp_pair(dt, c1, a, pair_v, s));
+            else conv(a, kTaps, EPI_POOL, l, 2 * lv.C, 0);
         } else {
             conv(conv_args(eng, W.enc[l][1], act(P.a[l]), lv.C, lv.R, EU, act(P.d[l]), lv.C), kTaps, EPI_STORE, l,
                  lv.C, 0);
@@ -1253,6 +1297,7 @@ pvf_status pvf_set_launch_variant(pvf_engine* eng, int i, int v)
     eng->kernels[i] = conv_kernel_name(eng->spec.compute_dtype, v, c.cin, c.taps, c.epi);
     name_first(eng);
     name_up(eng);
+    name_pair(eng);
     name_dec0(eng);
     return PVF_OK;
 }
@@ -1292,8 +1337,8 @@ pvf_status pvf_autotune(pvf_engine* eng, const pvf_tracks* tr, const pvf_vertice
                 // a transposed conv is not timed in a pass where it ran inside
                 // the launch before it
                 if (i > 0 && eng->conv[i - 1].up && fuses_up(eng, i - 1)) continue;
-                if (i + 1 < nl && eng->conv[i + 1].dec0 && fuses_dec0(eng, i + 1)) continue;
-                const float t = ms[i] + (eng->conv[i].first || eng->conv[i].dec0 ? ms[i - 1] : 0.f) +
+                if (i + 1 < nl && (fuses_dec0(eng, i + 1) || fuses_pair(eng, i + 1))) continue;
+                const float t = ms[i] + (eng->conv[i].first || eng->conv[i].pair || eng->conv[i].dec0 ? ms[i - 1] : 0.f) +
                                 (eng->conv[i].up ? ms[i + 1] : 0.f);
                 if (eng->conv[i].variant == v && t < best[i]) { best[i] = t; pick[i] = v; }
             }

@@ -319,6 +319,11 @@ int lp_default_up_variant(int n, int cin);
 // arguments, c2: dec0.c2 + head's.
 bool lp_dec0_ok(int variant);
 hipError_t launch_conv_lp_dec0(int dtype, const ConvArgs& c1, const ConvArgs& c2, int variant, hipStream_t s);
+// Variants of a max-pool launch that also compute the conv before it (both of
+// 64 output channels): the tensor between them stays in LDS.
+bool lp_pair_ok(int variant);
+hipError_t launch_conv_lp_pair(int dtype, const ConvArgs& c1, const ConvArgs& c2, int variant, hipStream_t s);
+std::string lp_pair_kernel_name(int dtype);
 bool fp8_dec0_ok(int variant);
 // enc0.c2 with the first convolution fused into its staging (FP8)
 hipError_t launch_conv_fp8_first(const ConvArgs& a, int variant, hipStream_t s);
