@@ -73,17 +73,27 @@ constexpr int occupancy_target(int lds_bytes, int waves_per_block)
     const int w = blocks * waves_per_block / 4;
     return w < 1 ? 1 : (w > 4 ? 4 : w);
 }
-template <int T_BYTES, int BM, int BN, int KC, int TAPS, int EPI, int STAGES, int XPAD>
+template <int T_BYTES, int BM, int BN, int KC, int TAPS, bool TILE, int STAGES, int XPAD>
 struct LpLds {
     static constexpr int stage = (BM + XPAD) * KC * T_BYTES + BN * TAPS * KC * T_BYTES;
-    static constexpr int v = Max<STAGES * stage, (EPI == EPI_HEAD ? 0 : BM * (BN + 8) * T_BYTES)>::v;
+    static constexpr int v = Max<STAGES * stage, (TILE ? BM * (BN + 8) * T_BYTES : 0)>::v;
 };
 
-// Epilogue shared by the conv kernels (the LDS passed in is free: every
-// wave is past its last read of the stage buffers).  The kernels issue the
-// MFMA as D^T = W X^T (weight fragment in the A slot), so lane (li, lg) of a
-// 16 x 16 tile holds channels 4 lg + v (v = 0..3) of tile row li: four
-// consecutive channels of one position, packed into one 8-byte LDS store.
+// Epilogue shared by the conv kernels.  The kernels issue the MFMA as
+// D^T = W X^T (weight fragment in the A slot), so lane (li, lg) of a 16 x 16
+// tile holds channels 4 lg + v (v = 0..3) of tile row li: four consecutive
+// channels of one position.
+//   Waves of 64 and more columns store straight from the registers: one
+// v_permlane16_swap per register turns the four-channel pieces of two
+// neighbouring column tiles into 16-byte ones, 64 bytes of a row per store,
+// and a max-pooling pair is two neighbouring lanes.  No LDS tile, no barrier:
+// the interval layout's enc2.c1 45.8 -> 43.8 us at 250 events, up1 43.7 ->
+// 41.2; the large batches wait on HBM either way (1 % to 3 %).
+//   Waves of 32 columns go through an LDS tile, whose rows give the pooled
+// row's stores all lanes (enc0.c2 at 97 events 20.6 us, 29.5 from the
+// registers), and so does EPI_UP, whose tile is an operand again.  The LDS
+// passed in is free: every wave is past its last read of the stages.
+constexpr bool lp_through_lds(int epi, int tnw) { return epi == EPI_UP || (epi != EPI_HEAD && tnw % 4 != 0); }
 template <class T, int NT, int BM, int BN, int WM, int TMW, int TNW, int EPI>
 __device__ __forceinline__ void lp_epilogue(const f32x4 (&acc)[TMW][TNW], const ConvArgs& a, void* lds, int64_t m0,
                                             int n0, int tid)
@@ -118,30 +128,34 @@ __device__ __forceinline__ void lp_epilogue(const f32x4 (&acc)[TMW][TNW], const 
         }
         return;
     } else {
-        T* ot = reinterpret_cast<T*>(lds);   // [BM][OP]
+        // biases of channels c .. c + 3 (n and cout are multiples of 8; columns beyond n are never stored)
+        struct Quad { float v[4]; };
+        auto quad = [](const float* p) __attribute__((always_inline)) { return *reinterpret_cast<const Quad*>(p); };
+        Quad b[TNW];
 #pragma unroll
         for (int j = 0; j < TNW; ++j) {
-            const int col = cw + j * 16 + 4 * lg;
-            const int n = n0 + col;
-            float b[4];
+            const int c = min(n0 + cw + j * 16 + 4 * lg, a.n - 4);
+            b[j] = quad(a.bias + (EPI == EPI_CONVT && c >= a.cout ? c - a.cout : c));
+        }
+        auto finish = [&](int i, int j) __attribute__((always_inline)) {
+            typedef T vec4 __attribute__((ext_vector_type(4)));
+            f32x4 x;
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
-                const int nv = min(n + v, a.n - 1);    // columns beyond n are never stored
-                b[v] = a.bias[EPI == EPI_CONVT ? nv % a.cout : nv];
+                x[v] = acc[i][j][v] + b[j].v[v];
+                if (EPI != EPI_CONVT) x[v] = lrelu(x[v], a.slope);
             }
+            return __builtin_bit_cast(uint2, __builtin_convertvector(x, vec4));
+        };
+        T* ot = reinterpret_cast<T*>(lds);   // [BM][OP]
+        if constexpr (lp_through_lds(EPI, TNW)) {
 #pragma unroll
-            for (int i = 0; i < TMW; ++i) {
-                T y[4];
+            for (int j = 0; j < TNW; ++j)
 #pragma unroll
-                for (int v = 0; v < 4; ++v) {
-                    float x = acc[i][j][v] + b[v];
-                    if (EPI != EPI_CONVT) x = lrelu(x, a.slope);
-                    y[v] = (T)x;
-                }
-                *reinterpret_cast<uint2*>(ot + (rw + i * 16 + li) * OP + col) = *reinterpret_cast<const uint2*>(y);
-            }
+                for (int i = 0; i < TMW; ++i)
+                    *reinterpret_cast<uint2*>(ot + (rw + i * 16 + li) * OP + cw + j * 16 + 4 * lg) = finish(i, j);
+            __syncthreads();
         }
-        __syncthreads();
         if constexpr (EPI == EPI_UP) {
             // The transposed conv of the tile (BN == n: every channel of its
             // rows is here): column c2 = tap * up_cout + o of the upsampled
@@ -203,44 +217,105 @@ __device__ __forceinline__ void lp_epilogue(const f32x4 (&acc)[TMW][TNW], const 
             }
             return;
         }
-        T* out = static_cast<T*>(a.out);
-        constexpr int CH = BN / 8;                  // 16-byte chunks per tile row
-        const int n_valid = a.n - n0 < BN ? a.n - n0 : BN;
-        for (int idx = tid; idx < BM * CH; idx += NT) {
-            const int row = idx / CH, q = idx % CH;
-            if (8 * q >= n_valid || m0 + row >= a.m_rows) continue;
-            int64_t e;
-            int loc;
-            rows.at(row, e, loc);
-            if (loc < kGuard || loc >= a.r_in - kGuard) continue;
-            const uint4 v = *reinterpret_cast<const uint4*>(ot + row * OP + 8 * q);
-            if constexpr (EPI == EPI_CONVT) {
-                const int n = n0 + 8 * q;
-                const int tj = n / a.cout, o = n - tj * a.cout;
-                const int64_t ro = e * a.r_out + kGuard + 2 * (loc - kGuard) + tj;
-                *reinterpret_cast<uint4*>(out + ro * a.ld_out + o) = v;
-            } else {
-                *reinterpret_cast<uint4*>(out + (m0 + row) * a.ld_out + n0 + 8 * q) = v;
-            }
-        }
-        if constexpr (EPI == EPI_POOL) {
-            T* pout = static_cast<T*>(a.pool_out);
-            for (int idx = tid; idx < (BM / 2) * CH; idx += NT) {
-                const int pr = idx / CH, q = idx % CH;
-                if (8 * q >= n_valid || m0 + 2 * pr >= a.m_rows) continue;   // even: first row of a pooling pair
+        if constexpr (lp_through_lds(EPI, TNW)) {
+            T* out = static_cast<T*>(a.out);
+            constexpr int CH = BN / 8;                  // 16-byte chunks per tile row
+            const int n_valid = a.n - n0 < BN ? a.n - n0 : BN;
+            for (int idx = tid; idx < BM * CH; idx += NT) {
+                const int row = idx / CH, q = idx % CH;
+                if (8 * q >= n_valid || m0 + row >= a.m_rows) continue;
                 int64_t e;
                 int loc;
-                rows.at(2 * pr, e, loc);
+                rows.at(row, e, loc);
                 if (loc < kGuard || loc >= a.r_in - kGuard) continue;
-                const uint4 r0 = *reinterpret_cast<const uint4*>(ot + (2 * pr) * OP + 8 * q);
-                const uint4 r1 = *reinterpret_cast<const uint4*>(ot + (2 * pr + 1) * OP + 8 * q);
-                const T* x0 = reinterpret_cast<const T*>(&r0);
-                const T* x1 = reinterpret_cast<const T*>(&r1);
-                T y[8];
+                const uint4 v = *reinterpret_cast<const uint4*>(ot + row * OP + 8 * q);
+                if constexpr (EPI == EPI_CONVT) {
+                    const int n = n0 + 8 * q;
+                    const int tj = n / a.cout, o = n - tj * a.cout;
+                    const int64_t ro = e * a.r_out + kGuard + 2 * (loc - kGuard) + tj;
+                    *reinterpret_cast<uint4*>(out + ro * a.ld_out + o) = v;
+                } else {
+                    *reinterpret_cast<uint4*>(out + (m0 + row) * a.ld_out + n0 + 8 * q) = v;
+                }
+            }
+            if constexpr (EPI == EPI_POOL) {
+                T* pout = static_cast<T*>(a.pool_out);
+                for (int idx = tid; idx < (BM / 2) * CH; idx += NT) {
+                    const int pr = idx / CH, q = idx % CH;
+                    if (8 * q >= n_valid || m0 + 2 * pr >= a.m_rows) continue;   // even: first row of a pooling pair
+                    int64_t e;
+                    int loc;
+                    rows.at(2 * pr, e, loc);
+                    if (loc < kGuard || loc >= a.r_in - kGuard) continue;
+                    const uint4 r0 = *reinterpret_cast<const uint4*>(ot + (2 * pr) * OP + 8 * q);
+                    const uint4 r1 = *reinterpret_cast<const uint4*>(ot + (2 * pr + 1) * OP + 8 * q);
+                    const T* x0 = reinterpret_cast<const T*>(&r0);
+                    const T* x1 = reinterpret_cast<const T*>(&r1);
+                    T y[8];
 #pragma unroll
-                for (int u = 0; u < 8; ++u) y[u] = (float)x0[u] >= (float)x1[u] ? x0[u] : x1[u];
-                const int64_t rp = e * a.r_pool + kGuard + (loc - kGuard) / 2;
-                *reinterpret_cast<uint4*>(pout + rp * a.ld_pool + n0 + 8 * q) = *reinterpret_cast<const uint4*>(y);
+                    for (int u = 0; u < 8; ++u) y[u] = (float)x0[u] >= (float)x1[u] ? x0[u] : x1[u];
+                    const int64_t rp = e * a.r_pool + kGuard + (loc - kGuard) / 2;
+                    *reinterpret_cast<uint4*>(pout + rp * a.ld_pool + n0 + 8 * q) = *reinterpret_cast<const uint4*>(y);
+                }
+            }
+            return;
+        } else {
+            T* out = static_cast<T*>(a.out);
+            static_assert(TNW % 4 == 0, "pairs of 16-byte pieces");
+            constexpr int NP = TNW / 2;
+            // after the swaps this lane's channels of column tiles 2 p, 2 p + 1
+            const int c0 = n0 + cw + 16 * (lg & 1) + 8 * (lg >> 1);
+            const bool odd = li & 1;
+#pragma unroll
+            for (int i = 0; i < TMW; ++i) {
+                u32x4 y[NP];
+#pragma unroll
+                for (int p = 0; p < NP; ++p) {
+                    const uint2 u = finish(i, 2 * p), w = finish(i, 2 * p + 1);
+                    const auto lo = __builtin_amdgcn_permlane16_swap(u.x, w.x, false, false);
+                    const auto hi = __builtin_amdgcn_permlane16_swap(u.y, w.y, false, false);
+                    y[p] = u32x4{lo[0], hi[0], lo[1], hi[1]};
+                }
+                const int t = rw + i * 16 + li;
+                int64_t e;
+                int loc;
+                rows.at(t, e, loc);
+                const bool ok = m0 + t < a.m_rows && loc >= kGuard && loc < a.r_in - kGuard;
+#pragma unroll
+                for (int p = 0; p < NP; ++p) {
+                    const int c = c0 + 32 * p;
+                    if (!ok || c >= a.n) continue;
+                    if constexpr (EPI == EPI_CONVT) {
+                        const int tj = c >= a.cout, o = c - tj * a.cout;
+                        const int64_t ro = e * a.r_out + kGuard + 2 * (loc - kGuard) + tj;
+                        *reinterpret_cast<u32x4*>(out + ro * a.ld_out + o) = y[p];
+                    } else {
+                        *reinterpret_cast<u32x4*>(out + (m0 + t) * a.ld_out + c) = y[p];
+                    }
+                }
+                if constexpr (EPI == EPI_POOL) {
+                    // rows t even and t + 1 are neighbouring lanes (m0 is even): of
+                    // two pieces the even lane pools the first, the odd lane the second
+                    T* pool = static_cast<T*>(a.pool_out) + (e * a.r_pool + kGuard + (loc - kGuard) / 2) * a.ld_pool;
+#pragma unroll
+                    for (int p = 0; p < NP; p += 2) {
+                        u32x4 x0, x1;
+#pragma unroll
+                        for (int k = 0; k < 4; ++k) {
+                            const unsigned below = __builtin_amdgcn_mov_dpp(y[p + 1][k], 0xB1, 0xF, 0xF, true);
+                            const unsigned above = __builtin_amdgcn_mov_dpp(y[p][k], 0xB1, 0xF, 0xF, true);
+                            x0[k] = odd ? below : y[p][k];
+                            x1[k] = odd ? y[p + 1][k] : above;
+                        }
+                        T m[8];
+                        const T* u0 = reinterpret_cast<const T*>(&x0);
+                        const T* u1 = reinterpret_cast<const T*>(&x1);
+#pragma unroll
+                        for (int k = 0; k < 8; ++k) m[k] = (float)u0[k] >= (float)u1[k] ? u0[k] : u1[k];
+                        const int c = c0 + 32 * (p + odd);
+                        if (ok && c < a.n) *reinterpret_cast<u32x4*>(pool + c) = *reinterpret_cast<const u32x4*>(m);
+                    }
+                }
             }
         }
     }
@@ -271,7 +346,7 @@ __device__ __forceinline__ void conv_lp_tile(const ConvArgs& a)
     constexpr int WPT = (WV + NT - 1) / NT;
     constexpr int OP = BN + 8;                  // epilogue tile pitch (elements)
     constexpr int STAGE = XROWS * KC + BN * TAPS * KC;
-    constexpr int SMEM = Max<STAGE, (EPI == EPI_HEAD ? 0 : BM * OP)>::v;
+    constexpr int SMEM = Max<STAGE, (lp_through_lds(EPI, TNW) ? BM * OP : 0)>::v;
 
     __shared__ __attribute__((aligned(16))) T smem[SMEM];
     T* xs = smem;
@@ -422,13 +497,13 @@ __device__ __forceinline__ void conv_lp_tile(const ConvArgs& a)
         }
     }
 
-    __syncthreads();   // the epilogue reuses the stage buffers
+    if constexpr (lp_through_lds(EPI, TNW)) __syncthreads();   // the epilogue reuses the stage buffers
     lp_epilogue<T, NT, BM, BN, WM, TMW, TNW, EPI>(acc, a, smem, m0, n0, tid);
 }
 
 template <class T, int WM, int WN, int TMW, int TNW, int KC, int PF, int TAPS, int EPI>
 __global__ __launch_bounds__(WM * WN * 64) __attribute__((amdgpu_waves_per_eu(PF ? 1 : occupancy_target(
-    LpLds<(int)sizeof(T), WM * TMW * 16, WN * TNW * 16, KC, TAPS, EPI, 1, TAPS - 1>::v, WM * WN))))
+    LpLds<(int)sizeof(T), WM * TMW * 16, WN * TNW * 16, KC, TAPS, lp_through_lds(EPI, TNW), 1, TAPS - 1>::v, WM * WN))))
 void conv_mfma_lp(ConvArgs a)
 {
     conv_lp_tile<T, WM, WN, TMW, TNW, KC, PF, TAPS, EPI, false>(a);
@@ -459,7 +534,7 @@ void conv_mfma_lp_first(ConvArgs a)
 // CU and cover each other's load latency, and one fragment buffer per wave.
 template <class T, int WM, int WN, int TMW, int TNW, int TAPS, int EPI, int NB>
 __global__ __launch_bounds__(WM * WN * 64) __attribute__((amdgpu_waves_per_eu(occupancy_target(
-    LpLds<(int)sizeof(T), WM * TMW * 16, WN * TNW * 16, 32, TAPS, EPI, NB, 16>::v, WM * WN))))
+    LpLds<(int)sizeof(T), WM * TMW * 16, WN * TNW * 16, 32, TAPS, lp_through_lds(EPI, TNW), NB, 16>::v, WM * WN))))
 void conv_mfma_lp_db(ConvArgs a)
 {
     using V = typename Lp<T>::vec8;
@@ -476,7 +551,7 @@ void conv_mfma_lp_db(ConvArgs a)
     constexpr int XI = XR / 16, WI = WRW / 16;      // wave-wide loads per stage
     constexpr int STAGE = (XR + WRW) * ROWB;         // bytes
     constexpr int OP = BN + 8;
-    constexpr int SMEM = Max<NB * STAGE, (EPI == EPI_HEAD ? 0 : BM * OP * (int)sizeof(T))>::v;
+    constexpr int SMEM = Max<NB * STAGE, (lp_through_lds(EPI, TNW) ? BM * OP * (int)sizeof(T) : 0)>::v;
     __shared__ __attribute__((aligned(16))) char smem[SMEM];
 
     const T* in = static_cast<const T*>(a.in);
@@ -584,7 +659,7 @@ void conv_mfma_lp_db(ConvArgs a)
             issue(0, (k + 1) * KC);
         }
     }
-    __syncthreads();   // the epilogue reuses the stage buffers
+    if constexpr (lp_through_lds(EPI, TNW)) __syncthreads();   // the epilogue reuses the stage buffers
     lp_epilogue<T, NT, BM, BN, WM, TMW, TNW, EPI>(acc, a, smem, m0, n0, tid);
 }
 
@@ -963,7 +1038,7 @@ void conv_mfma_lp_dec0d(ConvArgs c1, ConvArgs c2)
 // Two 5-tap convolutions with 64 output channels each and the max-pool in one
 // launch (enc1 of the 32-channel network): the 64-channel tensor between them
 // stays in LDS.  Apart they wait on HBM, which carries that tensor twice (half
-// the bytes of the two launches): 1000 events in BF16 250 us, fused 227; now
+// the bytes of the two launches): 1000 events in BF16 256 us, fused 218; now
 // the three loads a block waits for, and the matrix cores.  A block of 4 waves
 // owns BO = 240 output rows from m0:
 //   phase 1 computes c1's outputs for the BA = 256 rows from m0 - 2 (the tile
@@ -988,7 +1063,6 @@ void conv_mfma_lp_pair(ConvArgs c1, ConvArgs c2)
     constexpr int WI = kTaps * N / 16;                     // and of a weight stage (rows tap * 64 + column)
     constexpr int TILE = BA * ROWB;                        // one 32-channel tile of c1's output
     static_assert(XI * 16 * ROWB <= 2 * TILE, "the halo lies where the tiles go");
-    static_assert(BA * (N + 8) * (int)sizeof(T) <= 2 * TILE + WI * 16 * ROWB, "epilogue tile");
     __shared__ __attribute__((aligned(16))) char smem[2 * TILE + WI * 16 * ROWB];
     T* const xs = reinterpret_cast<T*>(smem);
     T* const ws = reinterpret_cast<T*>(smem + 2 * TILE);
@@ -1109,7 +1183,6 @@ void conv_mfma_lp_pair(ConvArgs c1, ConvArgs c2)
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
     stage(xs + BA * KC);
-    __syncthreads();       // the epilogue's tile takes the buffers
     const int64_t end = m0 + BO;
     if (end < c2.m_rows) c2.m_rows = (int)end;   // rows from BO on are the next block's
     lp_epilogue<T, NW * 64, BA, N, NW, 4, 4, EPI_POOL>(acc, c2, smem, m0, 0, tid);
