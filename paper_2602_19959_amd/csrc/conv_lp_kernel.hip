@@ -1551,12 +1551,14 @@ int lp_default_variant(int n, int cin, int taps, Epi epi)
 }
 
 // Decoder convs that run the following transposed conv in their epilogue
-// need a tile of all their output channels; the autotuner's BF16 picks at
-// 1000 events: 512 x 64 for 64 channels, the single-buffered direct-to-LDS
-// 256 x 128 for 128; -1 where no such variant fits.
+// need a tile of all their output channels: for 64 channels the single-buffered
+// direct-to-LDS 256 x 64 (dec1.c2 at 1000 events in BF16 176 us, 195 with the
+// register-staged 512 x 64; at 97 events 23 and 27), for 128 the same staging
+// in 256 x 128 (dec2.c2 243 us; 246 register-staged); -1 where no such variant
+// fits.
 int lp_default_up_variant(int n, int cin)
 {
-    const int v = n == 64 ? 22 : (n == 128 ? 26 : -1);
+    const int v = n == 64 ? 28 : (n == 128 ? 26 : -1);
     return v >= 0 && lp_variant_ok(v, n, cin, kTaps, EPI_UP) ? v : -1;
 }
 
@@ -1590,7 +1592,7 @@ int lp_batch_variant(int full, int n, int cin, Epi epi, int m_rows)
         v = tile_blocks(m_rows, n, 128, 32) <= kCus ? 33 : tile_blocks(m_rows, n, 256, 32) <= kCus ? 34 : full;
     } else if (epi == EPI_UP && n == 64) {
         // with the transposed conv in the epilogue, all columns in a block: 32,
-        // 64 or 128 rows (one event 2.7 us, 10 with the default 512 x 64; 32 events 9.2 and 12.4)
+        // 64 or 128 rows (one event 2.7 us, 10 with 512 x 64; 32 events 9.2 and 12.4)
         if (tile_blocks(m_rows, n, 32, 64) <= kCus) v = 40;
         else if (tile_blocks(m_rows, n, 64, 64) <= 2 * kCus) v = 41;
         else if (tile_blocks(m_rows, n, 128, 64) <= 2 * kCus) v = 4;
