@@ -242,9 +242,9 @@ const char *pvf_status_string(pvf_status s);
  * blocks (as many as fit on the device at once: four per compute unit for
  * histograms of up to 48 intervals, two for longer ones) takes them from a
  * device work queue, so heavy-tailed batches do not end on their largest
- * events; with up to 48 intervals the queue is skipped, and one block runs
- * per event, when the batch fits on the device at once.  persistent = 0: one
- * block per event.  Results are identical either way. */
+ * events; with up to 48 intervals the queue is skipped, and each event has a
+ * block (two in batches of up to 128 events), when the batch fits on the device
+ * at once.  persistent = 0: no queue for any batch.  Results are identical either way. */
 pvf_status pvf_set_track_schedule(pvf_engine *eng, int persistent);
 
 /* Capture the whole path for this batch view (its pointers and counts are
@@ -273,7 +273,11 @@ pvf_status pvf_graph_launch(pvf_engine *eng);
  * in BF16, FP16 and FP8 with 32 level-0 channels, the dec0.c1 slot enqueues
  * nothing when the head launch ("dec0.c2+head") takes a tile variant that
  * computes dec0.c1 in the same kernel (the default); its name then reads
- * "conv (in dec0.c2+head)". */
+ * "conv (in dec0.c2+head)".  In BF16 and FP16 the conv1 slot of an encoder
+ * level with 64 channels (enc1.c1 of the 32-channel network) likewise enqueues
+ * nothing when conv2 takes the tile variant that computes it (the default for
+ * batches that fill its tiles, while conv1's own variant is not set): "conv (in
+ * enc1.c2)". */
 int pvf_launch_count(const pvf_engine *eng);
 
 /* Name of launch i (e.g. "track", "enc0.c2", "up1", "peaks"); NULL if out

@@ -1641,6 +1641,8 @@ hipError_t launch_conv_lp_dec0(int dtype, const ConvArgs& c1, const ConvArgs& c2
 
 bool lp_pair_ok(int v) { return v >= 0 && v < kNumVariants && kVariants[v].pf == 8; }
 
+int lp_default_pair_variant() { return 42; }
+
 hipError_t launch_conv_lp_pair(int dtype, const ConvArgs& c1, const ConvArgs& c2, int v, hipStream_t s)
 {
     if (!lp_pair_ok(v) || c1.cin % 32 != 0 || c1.cin <= 0 || c1.n != 64 || c2.cin != 64 || c2.n != 64 ||

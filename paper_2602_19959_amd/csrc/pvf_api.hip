@@ -612,7 +612,7 @@ void build_names(pvf_engine* e)
             if (p < 1 || find("enc" + std::to_string(l) + ".c1") != p - 1) continue;
             auto& c = e->conv[p];
             c.pair = c.n == 64 && c.cin == 64 && e->conv[p - 1].n == 64;
-            if (c.pair) c.variant = 42;
+            if (c.pair) c.variant = lp_default_pair_variant();
         }
     name_pair(e);
     // dec0.c2 + head may compute dec0.c1 (the launch before it) itself

@@ -322,6 +322,7 @@ hipError_t launch_conv_lp_dec0(int dtype, const ConvArgs& c1, const ConvArgs& c2
 // Variants of a max-pool launch that also compute the conv before it (both of
 // 64 output channels): the tensor between them stays in LDS.
 bool lp_pair_ok(int variant);
+int lp_default_pair_variant();
 hipError_t launch_conv_lp_pair(int dtype, const ConvArgs& c1, const ConvArgs& c2, int variant, hipStream_t s);
 std::string lp_pair_kernel_name(int dtype);
 bool fp8_dec0_ok(int variant);
