@@ -11,7 +11,8 @@ Roofline: the dominant kernel is the kernel instance with the largest total
 time; its algorithmic FLOPs per launch (2 x MACs of the layers it runs, per
 event, times the events of one launch) over its average launch duration,
 measured with HIP events recorded by the library on the stream the kernels
-run on, against the MI355X dense FP32 matrix peak (157.3 TFLOP/s).
+run on, against the MI355X dense BF16 matrix peak over six in FP32 (2500 / 6 =
+417 TFLOP/s: six BF16 products make one of FP32) and its dtype's peak otherwise.
 
 CPU baseline: the FP64 oracle (plain C, threads over events; rebuilt for
 this host's CPU when gcc is there) on a bounded sample of the same batch, on
