@@ -11,20 +11,23 @@
 // BF16 of what the pieces before it leave), so a product of two FP32 values
 // is nine BF16 products.  Six of them are accumulated in FP32,
 //   hi*hi, hi*mid, mid*hi, mid*mid, hi*lo, lo*hi;
-// the three left out are below 2^-25 of the product, half an ulp of it.
+// the three left out add up to at most 2^-24 of the product, half an ulp of it.
+// The five small ones of a step (32 channels of one tap) are summed apart and
+// added to the accumulator once, so that it is rounded by one of the six
+// instructions and one addition instead of by all six.  Measured error against
+// FP64, relative 2-norm of p over 48 drawn calls (both widths and layouts, 1 to
+// 20 events), root mean square and largest: 2.6e-7 and 5.4e-7, against 6.2e-7 and
+// 1.2e-6 with the FP32 instruction and 5.3e-7 and 1.2e-6 with all six in one
+// chain; call by call 0.42 of the FP32 instruction's error on average and at most
+// 0.54 (one chain: 0.84 and 1.1).  The additions cost 4% to 5% of the time: 1000
+// events 9.08 -> 9.55 ms.
 // v_mfma_f32_16x16x4_f32 runs at 157 TFLOP/s dense, the BF16 form at 2.5
-// PFLOP/s, so six of those are 2.65 times as fast as one FP32 instruction;
-// the accumulator is rounded once per 32 products and instruction instead of
-// once per 4, and the measured error against FP64 is smaller: relative 2-norm
-// of p over 80 random networks, root mean square and largest, 4.2e-7 and 7.5e-7
-// with 32 channels (4.9e-7 and 9.5e-7 with the FP32 instruction), 5.9e-7 and
-// 9.3e-7 with 64 (6.8e-7 and 1.1e-6).  Most bins of a histogram are empty, so
-// one network's error is much one draw of the rounding, 0.55 to 1.9 times the
-// FP32 instruction's there and 0.86 on average.  Activations stay FP32 in HBM and are split while they are
-// staged; the weights are split once, at set-up.  Bound by the matrix rate at
-// the card's sustained clock: at 1000 events enc3.c2 takes 1.38 ms, 237 TFLOP/s
-// of FP32 work or 1.42 PFLOP/s of BF16 (2.37 ms and 138 TFLOP/s with the FP32
-// instruction, 86% of its peak), the whole network 9.2 ms (15.0 ms).
+// PFLOP/s, so six of those are 2.65 times as fast as one FP32 instruction.
+// Activations stay FP32 in HBM and are split while they are staged; the weights
+// are split once, at set-up.  Bound by the matrix rate at the card's sustained
+// clock: at 1000 events enc3.c2 takes 1.38 ms, 237 TFLOP/s of FP32 work or 1.42
+// PFLOP/s of BF16 (2.37 ms and 138 TFLOP/s with the FP32 instruction, 86% of its
+// peak), the whole network 9.6 ms (15.0 ms).
 //
 // A is never materialised: a block stages the (BM + 4) x 32 halo tile of input
 // rows once per 32-channel chunk in LDS, as three BF16 planes, and all five
@@ -68,7 +71,7 @@ __device__ __forceinline__ float lrelu(float x, float s) { return x >= 0.f ? x :
 
 // the products that are accumulated, smallest first: (weight piece, row piece), 0 = hi
 constexpr int kF32Products = 6;
-constexpr int kProd[kF32Products][2] = {{2, 0}, {0, 2}, {1, 1}, {1, 0}, {0, 1}, {0, 0}};
+constexpr int kProd[kF32Products][2] = {{0, 2}, {1, 1}, {2, 0}, {0, 1}, {1, 0}, {0, 0}};
 
 // Epilogue shared by the FP32 kernels, straight from the accumulators.  The
 // kernels issue the MFMA as D^T = W X^T (weight fragment in the A slot), so
@@ -208,11 +211,11 @@ template <int BM, int BN, int XB, int D, int TAPS> struct F32Lds {
     static constexpr int v = XB * x + D * w;
 };
 // Waves per SIMD handed to the register allocator: what the LDS allows on one
-// CU (160 KB), at most 2 for the 4 x 4-tile waves (64 accumulator and 96
-// fragment registers), 3 for the others.
+// CU (160 KB), at most 2 for the 4 x 4-tile waves (64 accumulator and 80
+// fragment and partial-sum registers), 4 for the others.
 template <int WM, int WN, int TMW, int TNW, int XB, int D, int TAPS> struct F32Occ {
-    static constexpr int w = 163840 / F32Lds<WM * TMW * 16, WN * TNW * 16, XB, D, TAPS>::v * WM * WN / 4;
-    static constexpr int most = TMW * TNW >= 16 ? 2 : 3;
+    static constexpr int w = (163840 / F32Lds<WM * TMW * 16, WN * TNW * 16, XB, D, TAPS>::v * WM * WN + 3) / 4;
+    static constexpr int most = TMW * TNW >= 16 ? 2 : 4;
     static constexpr int v = w < 1 ? 1 : w > most ? most : w;
 };
 
@@ -368,24 +371,38 @@ __device__ __forceinline__ void conv_f32_tile(const ConvArgs& a)
             if (tap == 0 && c + 1 < nc) x_fetch((c + 1) * KC);
             if (D > 2 || g + 1 < nk) w_issue(min(g + D - 1, nk - 1), ring == 0 ? D - 1 : ring - 1);
             const char* ws = smem + XB * Lds::x + ring * Lds::w + wn * TNW * kF32Pieces * FRAG + lane * 16;
-            bf16x8 wf[TNW][kF32Pieces], xf[TMW][kF32Pieces];
+            bf16x8 xf[TMW][kF32Pieces];
 #pragma unroll
-            for (int q = 0; q < kF32Pieces; ++q) {
-#pragma unroll
-                for (int j = 0; j < TNW; ++j)
-                    wf[j][q] = *reinterpret_cast<const bf16x8*>(ws + (j * kF32Pieces + q) * FRAG);
+            for (int q = 0; q < kF32Pieces; ++q)
 #pragma unroll
                 for (int i = 0; i < TMW; ++i)
                     xf[i][q] = *reinterpret_cast<const bf16x8*>(xs + q * 4 * PLANE + (i * 16 + tap) * 16);
-            }
 #pragma unroll
-            for (int t = 0; t < kF32Products; ++t)
+            for (int j0 = 0; j0 < TNW; j0 += 2) {
+                bf16x8 wf[2][kF32Pieces];
+#pragma unroll
+                for (int q = 0; q < kF32Pieces; ++q)
+#pragma unroll
+                    for (int j = 0; j < 2; ++j)
+                        wf[j][q] = *reinterpret_cast<const bf16x8*>(ws + ((j0 + j) * kF32Pieces + q) * FRAG);
+                f32x4 low[TMW][2];                 // the step's five smaller products
+#pragma unroll
+                for (int t = 0; t < kF32Products; ++t)
+#pragma unroll
+                    for (int i = 0; i < TMW; ++i)
+#pragma unroll
+                        for (int j = 0; j < 2; ++j) {
+                            f32x4& d = t + 1 < kF32Products ? low[i][j] : acc[i][j0 + j];
+                            d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[j][kProd[t][0]], xf[i][kProd[t][1]],
+                                                                        t == 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : d, 0, 0, 0);
+                        }
 #pragma unroll
                 for (int i = 0; i < TMW; ++i)
 #pragma unroll
-                    for (int j = 0; j < TNW; ++j)
-                        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[j][kProd[t][0]], xf[i][kProd[t][1]],
-                                                                            acc[i][j], 0, 0, 0);
+                    for (int j = 0; j < 2; ++j)
+#pragma unroll
+                        for (int v = 0; v < 4; ++v) acc[i][j0 + j][v] += low[i][j][v];
+            }
             if (XB == 2 && tap == TAPS - 1 && c + 1 < nc) x_store((c + 1) & 1, (c + 1) * KC);
             ring = ring + 1 == D ? 0 : ring + 1;
         }
