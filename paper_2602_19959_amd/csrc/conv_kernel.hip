@@ -53,6 +53,8 @@
 // conv_mfma_f32_first runs enc0.c2 with the first convolution (one input
 // channel, five taps) computed in its halo staging from the histogram rows,
 // so that 32-channel tensor never goes through HBM.
+#include <cmath>
+
 #include "pvf_internal.h"
 
 namespace pvf {
@@ -72,6 +74,18 @@ __device__ __forceinline__ float lrelu(float x, float s) { return x >= 0.f ? x :
 // the products that are accumulated, smallest first: (weight piece, row piece), 0 = hi
 constexpr int kF32Products = 6;
 constexpr int kProd[kF32Products][2] = {{0, 2}, {1, 1}, {2, 0}, {0, 1}, {1, 0}, {0, 0}};
+
+// The top of FP32's range.  Values from kBf16Cut on round to infinity in BF16;
+// and where hi*hi overflows, as FP32 does there, a smaller product of a rounded
+// piece may overflow to the other sign, a sum of NaN.  Pieces that are cut off
+// instead of rounded have the value's own sign.  Row values are cut off where
+// their products may reach 2^127, w_sum being the layer's largest sum of
+// |weight| over an output channel (f32_split_cut).  Weights are rounded where
+// that sum is at most kRoundSum: their smaller pieces' products are below 2^-8
+// of theirs, so they stay below 2^127 over finite rows; else they are cut off
+// too.  (Sums within 2^-7 of FP32's largest value may round up to infinity.)
+constexpr float kBf16Cut = 0x1.ffp127f;
+constexpr float kRoundSum = 0x1p7f;
 
 // Epilogue shared by the FP32 kernels, straight from the accumulators.  The
 // kernels issue the MFMA as D^T = W X^T (weight fragment in the A slot), so
@@ -159,9 +173,32 @@ __device__ __forceinline__ void f32_epilogue(const f32x4 (&acc)[TMW][TNW], const
 
 // Eight FP32 values as three planes of eight BF16 values; the pieces add up
 // to the value exactly (24 significant bits; below 2^-103 the last piece
-// loses bits to BF16's subnormals).
-__device__ __forceinline__ void split8(const f32x4& x0, const f32x4& x1, u32x4 (&p)[kF32Pieces])
+// loses bits to BF16's subnormals).  From `cut` on they are cut off instead of
+// rounded.  An infinity is (0, 0, infinity): its last piece meets only the
+// weight's first, so its product has the right sign.
+__device__ __forceinline__ void split8(const f32x4& x0, const f32x4& x1, float cut, u32x4 (&p)[kF32Pieces])
 {
+    float most = 0.f;
+#pragma unroll
+    for (int k = 0; k < 4; ++k)    // fmaxf would first quiet every operand, twice the instructions
+        asm("v_max3_f32 %0, |%1|, |%2|, %0" : "+v"(most) : "v"(x0[k]), "v"(x1[k]));
+    if (__builtin_expect(most >= cut, 0)) {
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+            const float x = k < 4 ? x0[k & 3] : x1[k & 3];
+            const bool large = fabsf(x) >= cut, inf = isinf(x);
+            float r = x;
+#pragma unroll
+            for (int q = 0; q < kF32Pieces; ++q) {
+                float y = large ? __builtin_bit_cast(float, __builtin_bit_cast(unsigned, r) & 0xffff0000u) : (float)(__bf16)r;
+                if (inf) y = q + 1 < kF32Pieces ? 0.f : x;
+                r -= y;
+                const unsigned u = __builtin_bit_cast(unsigned, y);
+                p[q][k >> 1] = k & 1 ? p[q][k >> 1] | (u & 0xffff0000u) : u >> 16;
+            }
+        }
+        return;
+    }
 #pragma unroll
     for (int h = 0; h < 4; ++h) {
         f32x2 r = h < 2 ? f32x2{x0[2 * h], x0[2 * h + 1]} : f32x2{x1[2 * h - 4], x1[2 * h - 3]};
@@ -180,7 +217,7 @@ __device__ __forceinline__ void split8(const f32x4& x0, const f32x4& x1, u32x4 (
 // Set-up: weights [n][taps][cin] -> per 32-channel chunk, tap, group of 16
 // columns and piece one 1 KB fragment, in which lane l holds channels
 // 8 (l / 16) .. + 7 of column l % 16.  One thread per lane of a fragment group.
-__global__ __launch_bounds__(256) void split_weights(const float* w, int n, int taps, int cin, uint16_t* pieces)
+__global__ __launch_bounds__(256) void split_weights(const float* w, int n, int taps, int cin, float cut, uint16_t* pieces)
 {
     const int t = blockIdx.x * 256 + threadIdx.x;
     const int lane = t & 63, group = t >> 6;           // group = (chunk * taps + tap) * (n / 16) + column group
@@ -190,7 +227,7 @@ __global__ __launch_bounds__(256) void split_weights(const float* w, int n, int 
     const f32x4* src = reinterpret_cast<const f32x4*>(w + ((int64_t)(16 * cg + lane % 16) * taps + tap) * cin +
                                                       KC * chunk + 8 * (lane / 16));
     u32x4 p[kF32Pieces];
-    split8(src[0], src[1], p);
+    split8(src[0], src[1], cut, p);
 #pragma unroll
     for (int q = 0; q < kF32Pieces; ++q)
         *reinterpret_cast<u32x4*>(reinterpret_cast<char*>(pieces) + ((int64_t)group * kF32Pieces + q) * FRAG + lane * 16) = p[q];
@@ -292,7 +329,7 @@ __device__ __forceinline__ void conv_f32_tile(const ConvArgs& a)
     };
     auto x_put = [&](char* xs, int u, const f32x4& y0, const f32x4& y1) __attribute__((always_inline)) {
         u32x4 p[kF32Pieces];
-        split8(y0, y1, p);
+        split8(y0, y1, a.split_cut, p);
 #pragma unroll
         for (int q = 0; q < kF32Pieces; ++q)
             *reinterpret_cast<u32x4*>(xs + (q * 4 + oct) * PLANE + (row0 + u * RS) * 16) = p[q];
@@ -536,13 +573,16 @@ hipError_t dispatch(int v, const ConvArgs& a, hipStream_t s)
 
 }  // namespace
 
-hipError_t launch_split_weights(const float* w, int n, int taps, int cin, uint16_t* pieces, hipStream_t s)
+hipError_t launch_split_weights(const float* w, int n, int taps, int cin, float w_sum, uint16_t* pieces, hipStream_t s)
 {
     if (n % 16 != 0 || cin % KC != 0) return hipErrorInvalidValue;
     const unsigned threads = (unsigned)(n / 16 * taps * (cin / KC)) * 64;
-    hipLaunchKernelGGL(split_weights, dim3((threads + 255) / 256), dim3(256), 0, s, w, n, taps, cin, pieces);
+    hipLaunchKernelGGL(split_weights, dim3((threads + 255) / 256), dim3(256), 0, s, w, n, taps, cin,
+                       w_sum > kRoundSum ? 0.f : kBf16Cut, pieces);
     return hipGetLastError();
 }
+
+float f32_split_cut(float w_sum) { return std::fmin(kBf16Cut, 0x1p127f / w_sum); }
 
 int f32_variant_count() { return kNumVariants; }
 

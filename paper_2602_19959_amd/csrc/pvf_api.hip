@@ -397,6 +397,7 @@ struct pvf_engine {
         int variant = -1;
         bool pinned = false;          // variant set by the caller or the autotuner: every batch runs it
         const WeightLayout::Conv* w = nullptr;
+        float split_cut = 0.f;        // FP32: ConvArgs::split_cut
         std::vector<int> in_src;      // launches whose stored outputs form this input, in channel order
         size_t col = 0;               // FP8: offsets (floats) into the scales region
         size_t fold = 0;              // FP8 stored outputs: [n] s_n / a_out, then [n] bias / a_out
@@ -640,6 +641,21 @@ void build_names(pvf_engine* e)
 bool misaligned(const void* p, size_t a) { return (reinterpret_cast<uintptr_t>(p) % a) != 0; }
 
 
+// Largest sum of |w| over a row of w [n][k] (k a multiple of 16).
+float largest_row_sum(const float* w, int n, int k)
+{
+    float most = 0.f;
+    for (int r = 0; r < n; ++r, w += k) {
+        float lane[16] = {};                 // sixteen partial sums, for the vector units
+        for (int i = 0; i < k; i += 16)
+            for (int j = 0; j < 16; ++j) lane[j] += std::fabs(w[i + j]);
+        float sum = 0.f;
+        for (float x : lane) sum += x;
+        most = std::max(most, sum);
+    }
+    return most;
+}
+
 // The track network's layers inside the packed FP32 weights (blob order):
 // W [N][K] row-major, then b [N].
 struct MlpLayer { size_t w, b; int k, n; };
@@ -861,6 +877,7 @@ pvf_status enqueue(pvf_engine* eng, const pvf_tracks* tr, const pvf_vertices* ou
     float* scales = dt == PVF_FP8_E4M3 ? at<float>(eng, eng->plan.scales) : nullptr;
     // one UNet convolution: FP8 scales of this launch, launch, then calibration
     auto conv = [&](ConvArgs a, int taps, Epi epi, int store_level, int store_ld, int store_ch_off) {
+        a.split_cut = eng->conv[li].split_cut;
         if (scales) {
             a.col_scale = scales + eng->conv[li].col;
             a.out_inv_scale = epi == EPI_HEAD ? nullptr : scales + eng->outinv_off[li];
@@ -1124,11 +1141,14 @@ static pvf_status init_impl(const pvf_spec* spec, const void* blob, size_t blob_
                                  e->stream);
     } else if (err == hipSuccess && spec->compute_dtype == PVF_FP32) {
         // split on the device, from the FP32 weights just uploaded
-        for (const auto& c : e->conv)
-            if (c.variant >= 0 && err == hipSuccess)
-                err = launch_split_weights(reinterpret_cast<const float*>(e->arena + plan.weights) + c.w->w, c.n, c.taps, c.cin,
+        for (auto& c : e->conv)
+            if (c.variant >= 0 && err == hipSuccess) {
+                const float most = largest_row_sum(&packed[c.w->w], c.n, c.taps * c.cin);
+                c.split_cut = f32_split_cut(most);
+                err = launch_split_weights(reinterpret_cast<const float*>(e->arena + plan.weights) + c.w->w, c.n, c.taps, c.cin, most,
                                            reinterpret_cast<uint16_t*>(e->arena + plan.weights_lp) + kF32Pieces * c.w->w,
                                            e->stream);
+            }
     } else if (err == hipSuccess) {
         pack_weights_lp(e->wl, b.shape, packed, spec->compute_dtype, packed_lp);
         const int dt = spec->compute_dtype;

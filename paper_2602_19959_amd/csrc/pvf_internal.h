@@ -129,6 +129,7 @@ struct ConvArgs {
     int m_rows;          // total input rows (= events * R_in)
     int r_in;            // rows per event of the input level
     const void* w;       // packed [N][taps][cin] (element type = compute dtype; FP32: fragments of BF16 pieces)
+    float split_cut;     // FP32: row values from here on are cut off into their pieces, not rounded
     const float* bias;   // [Cout]
     int n;               // GEMM N (Cout, or 2*Cout for the transposed conv)
     float slope;         // LeakyReLU slope
@@ -296,7 +297,10 @@ std::string conv_kernel_name(int dtype, int variant, int cin, int taps, Epi epi)
 hipError_t launch_conv_f32(const ConvArgs& a, int taps, Epi epi, int variant, hipStream_t s);
 // Set-up: FP32 conv weights w [n][taps][cin] as BF16 pieces, in the order the
 // FP32 tiles read them (3 * n * taps * cin values).
-hipError_t launch_split_weights(const float* w, int n, int taps, int cin, uint16_t* pieces, hipStream_t s);
+hipError_t launch_split_weights(const float* w, int n, int taps, int cin, float w_sum, uint16_t* pieces, hipStream_t s);
+// ConvArgs::split_cut of that launch.  w_sum: the largest sum of |weight| over
+// an output channel.
+float f32_split_cut(float w_sum);
 int f32_variant_count();
 bool f32_variant_ok(int variant, int n, int taps, Epi epi);
 int f32_default_variant(int n, int cin, int taps, Epi epi);
