@@ -219,10 +219,10 @@ pvf_status pvf_execute_on(pvf_engine *eng, const pvf_tracks *tracks, const pvf_v
  * 1.8 MiB in FP8: 8, 17 and 35 events); a larger batch returns
  * PVF_ERR_SCRATCH_TOO_SMALL and enqueues nothing.  The other checks are
  * those of pvf_execute.
- * Sharing: an engine takes the area with the fewest live engines on its
- * device at initialisation and gives it back in pvf_destroy (after its work is
- * done), so up to PVF_SCRATCH_AREAS engines have one each; further engines
- * share.  An area keeps the last call's contents (each call clears what it
+ * Sharing: an engine takes the area with the fewest engines on it at its first
+ * call here and gives it back in pvf_destroy, so up to PVF_SCRATCH_AREAS engines
+ * that make scratch calls have one each, however many others there are; further
+ * ones share.  An area keeps the last call's contents (each call clears what it
  * needs zeroed, on the stream, before its kernels).  Calls on one area that
  * overlap in time race and corrupt each other's results: order them on one
  * stream, or with events.  pvf_debug_tensor views only pvf_execute calls.

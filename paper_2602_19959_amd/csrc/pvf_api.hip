@@ -386,7 +386,8 @@ struct pvf_engine {
     float leaky = 0.f, s_in = 0.f, head_b = 0.f;
     float shift[kFeat] = {}, scale[kFeat] = {};
     char* arena = nullptr;
-    char* scratch = nullptr;             // this engine's scratch area on its device
+    bool has_scratch = false;            // the device's scratch areas could be found
+    char* scratch = nullptr;             // this engine's area, from its first scratch call on
     int device = 0;
     hipStream_t stream = nullptr;
     std::vector<std::string> names;      // one per launch of pvf_execute
@@ -1167,7 +1168,7 @@ static pvf_status init_impl(const pvf_spec* spec, const void* blob, size_t blob_
         delete e;
         return PVF_ERR_DEVICE;
     }
-    e->scratch = scratch_take(dev);      // for pvf_execute_scratch, until pvf_destroy
+    e->has_scratch = scratch_resolve(dev);   // set-up of pvf_execute_scratch, once per device
     *out = e;
     return PVF_OK;
 }
@@ -1226,11 +1227,12 @@ pvf_status pvf_execute_scratch(pvf_engine* eng, const pvf_tracks* tr, const pvf_
 {
     pvf_status st = check_call(eng, tr, out);
     if (st != PVF_OK || tr->n_events == 0) return st;
-    if (!eng->scratch) return PVF_ERR_DEVICE;
+    if (!eng->has_scratch) return PVF_ERR_DEVICE;
     // the per-batch regions laid out for this batch alone, from the scratch's start
     Plan P = eng->plan;
     P.total = layout_work(&eng->spec, tr->n_events, 0, &P);
     if (P.total > kScratchBytes) return PVF_ERR_SCRATCH_TOO_SMALL;
+    if (!eng->scratch) eng->scratch = scratch_take(eng->device);
     // zero padding: the guard rows of every activation tensor
     const size_t eb = (size_t)act_bytes(eng->spec.compute_dtype);
     GuardZeroArgs g{};
@@ -1276,7 +1278,7 @@ const char* pvf_status_string(pvf_status s)
     case PVF_ERR_DEVICE: return "HIP runtime error";
     case PVF_ERR_ALIGNMENT: return "misaligned buffer";
     case PVF_ERR_SCRATCH_TOO_SMALL:
-        return "batch too large for the library's fixed scratch (PVF_SCRATCH_BYTES = 64 MiB per device)";
+        return "batch too large for the library's fixed scratch (PVF_SCRATCH_BYTES = 64 MiB)";
     }
     return "unknown status";
 }

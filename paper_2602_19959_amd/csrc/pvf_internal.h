@@ -366,9 +366,11 @@ struct GuardZeroArgs {
     int n;               // regions
     int64_t n_seq;       // sequences per region
 };
-// A scratch area of `device` (which must be current) for one engine, the one
-// with the fewest engines on it, and its return; nullptr if the device address
-// could not be obtained.  Any thread.
+// Look up the areas' address on `device` (which must be current); false if it
+// could not be obtained.  Then: an area of the device for one engine, the one
+// with the fewest engines on it, and its return.  Any thread; taking and
+// returning make no HIP calls.
+bool scratch_resolve(int device);
 char* scratch_take(int device);
 void scratch_give_back(int device, const char* area);
 // Clear the kGuard rows at both ends of every sequence of every region.

@@ -2,8 +2,8 @@
 // (callers that cannot allocate device memory).
 //
 // There are kScratchSlots of them on a device.  An engine takes the one with
-// the fewest live engines when it is made and gives it back when it is
-// destroyed, so calls of up to kScratchSlots engines may overlap on a device
+// the fewest engines on it at its first scratch call, so that engines without
+// such calls take none, and gives it back when it is destroyed.  Calls of up to kScratchSlots engines may therefore overlap on a device
 // (three one-event engines in turn then run side by side, where one area would
 // have them corrupt each other or wait).
 //
@@ -35,7 +35,7 @@ constexpr int kMaxDevices = 64;
 std::mutex g_lock;
 bool g_resolved[kMaxDevices] = {};
 char* g_ptr[kMaxDevices] = {};
-int g_users[kMaxDevices][kScratchSlots] = {};   // live engines on each area
+int g_users[kMaxDevices][kScratchSlots] = {};   // engines on each area
 
 // Zero the first and last kGuard rows of every sequence of region blockIdx.y;
 // 4-byte stores (row sizes are multiples of 4 bytes).
@@ -56,20 +56,27 @@ __global__ __launch_bounds__(256) void zero_guard_rows(GuardZeroArgs a)
 
 }  // namespace
 
+bool scratch_resolve(int device)
+{
+    if (device < 0 || device >= kMaxDevices) return false;
+    std::lock_guard<std::mutex> lock(g_lock);
+    if (g_resolved[device]) return true;
+    void* p = nullptr;
+    const hipError_t err = hipGetSymbolAddress(&p, HIP_SYMBOL(scratch));
+    if (err != hipSuccess) {
+        (void)hipGetLastError();   // leave no sticky error for the caller's next call
+        return false;              // not cached: a later init on this device retries
+    }
+    g_ptr[device] = static_cast<char*>(p);
+    g_resolved[device] = true;
+    return true;
+}
+
 char* scratch_take(int device)
 {
     if (device < 0 || device >= kMaxDevices) return nullptr;
     std::lock_guard<std::mutex> lock(g_lock);
-    if (!g_resolved[device]) {
-        void* p = nullptr;
-        const hipError_t err = hipGetSymbolAddress(&p, HIP_SYMBOL(scratch));
-        if (err != hipSuccess) {
-            (void)hipGetLastError();   // leave no sticky error for the caller's next call
-            return nullptr;            // not cached: a later init on this device retries
-        }
-        g_ptr[device] = static_cast<char*>(p);
-        g_resolved[device] = true;
-    }
+    if (!g_resolved[device]) return nullptr;
     int slot = 0;
     for (int k = 1; k < kScratchSlots; ++k)
         if (g_users[device][k] < g_users[device][slot]) slot = k;
