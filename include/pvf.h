@@ -229,7 +229,10 @@ pvf_status pvf_execute_on(pvf_engine *eng, const pvf_tracks *tracks, const pvf_v
  * PVF_ERR_DEVICE if the scratch's device address could not be obtained. */
 pvf_status pvf_execute_scratch(pvf_engine *eng, const pvf_tracks *tracks, const pvf_vertices *out);
 
-/* Release the engine's host state.  The arena is the caller's to free. */
+/* Release the engine's host state.  The arena is the caller's to free.  An
+ * engine that has made scratch calls first waits for its stream's work (unless
+ * the stream is being captured), as its scratch area may go to another engine;
+ * graphs of the caller's own that hold its scratch calls must have ended. */
 pvf_status pvf_destroy(pvf_engine *eng);
 
 /* Static English text of a status code. */

@@ -1254,13 +1254,30 @@ pvf_status pvf_execute_scratch(pvf_engine* eng, const pvf_tracks* tr, const pvf_
     return enqueue(eng, tr, out, eng->stream, P, eng->scratch);
 }
 
+// Wait for a stream's work; not while it is being captured (the wait would
+// end the capture), and without ending captures that other threads have open.
+static void wait_for(hipStream_t s)
+{
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    const bool relaxed = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
+    hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &capturing) == hipSuccess && capturing == hipStreamCaptureStatusNone)
+        (void)hipStreamSynchronize(s);
+    if (relaxed) (void)hipThreadExchangeStreamCaptureMode(&mode);
+    (void)hipGetLastError();
+}
+
 pvf_status pvf_destroy(pvf_engine* eng)
 {
     if (!eng) return PVF_ERR_INVALID_ARGUMENT;
     if (eng->graph_exec) (void)hipGraphExecDestroy(eng->graph_exec);
     if (eng->graph) (void)hipGraphDestroy(eng->graph);
     for (hipEvent_t ev : eng->events) (void)hipEventDestroy(ev);
-    scratch_give_back(eng->device, eng->scratch);
+    if (eng->scratch) {
+        // the area's next user may not meet this engine's calls still running
+        wait_for(eng->stream);
+        scratch_give_back(eng->device, eng->scratch);
+    }
     delete eng;
     return PVF_OK;
 }

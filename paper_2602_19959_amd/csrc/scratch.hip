@@ -3,7 +3,8 @@
 //
 // There are kScratchSlots of them on a device.  An engine takes the one with
 // the fewest engines on it at its first scratch call, so that engines without
-// such calls take none, and gives it back when it is destroyed.  Calls of up to kScratchSlots engines may therefore overlap on a device
+// such calls take none, and gives it back when it is destroyed, once its work is
+// done.  Calls of up to kScratchSlots engines may therefore overlap on a device
 // (three one-event engines in turn then run side by side, where one area would
 // have them corrupt each other or wait).
 //
