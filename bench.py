@@ -347,7 +347,7 @@ def gemm_yardstick(args):
     feat, off = pv.upload_events(batch)
     out = eng.alloc_outputs(E, with_prob=False)
     eng.profile(True)
-    names, kernels = eng.launch_names(), eng.launch_kernels()
+    names, kernels = eng.launch_names(), eng.launch_kernels(E)
     runs = []
     for r in range(args.warmup + args.steps):
         eng.execute(feat, off, out)
@@ -507,7 +507,7 @@ def main():
             picked = eng.autotune(feat, off, eng.alloc_outputs(E, with_prob=False), reps=2)
             print(f"[bench] autotuned in {time.perf_counter() - t_tune:.1f} s: "
                   + ", ".join(f"{n}={v}" for n, v in zip(names, picked) if v >= 0), file=sys.stderr, flush=True)
-        kernels = eng.launch_kernels()
+        kernels = eng.launch_kernels(E)
         print(f"[bench] E={E} mix={args.mix} tracks={int(T.sum())} arena={eng.arena_bytes / 1e9:.2f} GB "
               f"launches={len(names)}", file=sys.stderr, flush=True)
 

@@ -288,13 +288,18 @@ int pvf_launch_count(const pvf_engine *eng);
 const char *pvf_launch_name(const pvf_engine *eng, int i);
 
 /* Kernel that launch i runs for full batches, as it appears in a profiler's
- * kernel name (unless a variant was set, by pvf_set_launch_variant or
- * pvf_autotune, a batch too small to fill the device runs a smaller tile shape
- * of it, with the same bits;
- * e.g. "conv_mfma_f32<4, 2, 2, 4, 5, 0>", "track_stage"); NULL if out of
- * range.  Owned by the engine; valid until the next pvf_set_launch_variant,
- * pvf_autotune or pvf_set_track_schedule on it. */
+ * kernel name (e.g. "conv_mfma_f32<4, 2, 2, 4, 2, 5, 0>", "track_stage"); NULL
+ * if out of range.  Owned by the engine; valid until the next
+ * pvf_set_launch_variant, pvf_autotune or pvf_set_track_schedule on it. */
 const char *pvf_launch_kernel(const pvf_engine *eng, int i);
+
+/* Kernel that launch i runs in a call of n_events events: unless a variant was
+ * set, by pvf_set_launch_variant or pvf_autotune, a batch too small to fill the
+ * device runs smaller tile shapes, or one launch's work in two, with the same
+ * bits.  NULL if i is out of range, or n_events is not from 1 to max_events.
+ * Owned by the engine; valid until the next such call for another batch size and
+ * the calls named above. */
+const char *pvf_launch_kernel_at(pvf_engine *eng, int i, int32_t n_events);
 
 /* Tile-shape variants (Section 5 of the paper: launch-geometry tuning).
  * A UNet convolution launch can run any of several tile shapes; every

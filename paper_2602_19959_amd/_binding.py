@@ -123,6 +123,8 @@ def load_library() -> C.CDLL:
     lib.pvf_launch_name.restype = C.c_char_p
     lib.pvf_launch_kernel.argtypes = [vp, C.c_int]
     lib.pvf_launch_kernel.restype = C.c_char_p
+    lib.pvf_launch_kernel_at.argtypes = [vp, C.c_int, i32]
+    lib.pvf_launch_kernel_at.restype = C.c_char_p
     lib.pvf_launch_variant_count.argtypes = [vp, C.c_int]
     lib.pvf_launch_variant_count.restype = C.c_int
     lib.pvf_launch_variant.argtypes = [vp, C.c_int]
@@ -338,9 +340,14 @@ class Engine:
         n = self.lib.pvf_launch_count(self.handle)
         return [self.lib.pvf_launch_name(self.handle, i).decode() for i in range(n)]
 
-    def launch_kernels(self) -> list:
+    def launch_kernels(self, n_events: int | None = None) -> list:
+        """Kernel of each launch in a full batch, or in a call of n_events."""
         n = self.lib.pvf_launch_count(self.handle)
-        return [self.lib.pvf_launch_kernel(self.handle, i).decode() for i in range(n)]
+        if n_events is None:
+            return [self.lib.pvf_launch_kernel(self.handle, i).decode() for i in range(n)]
+        if not 1 <= n_events <= self.spec.max_events:
+            raise ValueError("n_events must be from 1 to max_events")
+        return [self.lib.pvf_launch_kernel_at(self.handle, i, n_events).decode() for i in range(n)]
 
     def variants(self) -> list:
         """Current variant of each launch (-1 for launches without variants)."""

@@ -391,8 +391,10 @@ struct pvf_engine {
     int device = 0;
     hipStream_t stream = nullptr;
     std::vector<std::string> names;      // one per launch of pvf_execute
-    std::vector<std::string> kernels;    // kernel instance of each launch
+    std::vector<std::string> kernels;    // kernel instance of each launch in a full batch
+    std::vector<std::string> kernels_at; // and of the batch size last asked for (pvf_launch_kernel_at)
     struct ConvLaunch {
+        int level = 0;                // of the input rows
         int n = 0, cin = 0, taps = 0, cout = 0;
         Epi epi = EPI_STORE;
         int variant = -1;
@@ -479,60 +481,46 @@ bool fuses_pair(const pvf_engine* e, int i, int v)
 }
 bool fuses_pair(const pvf_engine* e, int i) { return fuses_pair(e, i, e->conv[i].variant); }
 
-// Kernel names of an encoder level's two convs for conv2's current variant.
-void name_pair(pvf_engine* e)
+// Kernel of every launch in a call of n_events events (0: a full batch).
+std::vector<std::string> kernel_names(const pvf_engine* e, int n_events)
 {
     const int dt = e->spec.compute_dtype;
-    for (size_t i = 1; i < e->conv.size(); ++i) {
+    auto variant = [&](size_t i) {
         const auto& c = e->conv[i];
-        if (!c.pair) continue;
-        const auto& p = e->conv[i - 1];
-        const bool f = fuses_pair(e, (int)i);
-        e->kernels[i] = f ? lp_pair_kernel_name(dt) : conv_kernel_name(dt, c.variant, c.cin, c.taps, c.epi);
-        e->kernels[i - 1] = f ? "conv (in " + e->names[i] + ")" : conv_kernel_name(dt, p.variant, p.cin, p.taps, p.epi);
-    }
-}
-
-// Kernel names of dec0.c1 and dec0.c2 + head for the head's current variant.
-void name_dec0(pvf_engine* e)
-{
-    const int dt = e->spec.compute_dtype;
-    for (size_t i = 1; i < e->conv.size(); ++i) {
+        return n_events > 0 ? tile(e, (int)i, n_events * e->plan.units * e->plan.lv[c.level].R) : c.variant;
+    };
+    auto conv_name = [&](size_t i, Epi epi) {
         const auto& c = e->conv[i];
-        if (!c.dec0) continue;
-        const auto& p = e->conv[i - 1];
-        const bool f = fuses_dec0(e, (int)i);
-        e->kernels[i] = conv_kernel_name(dt, c.variant, c.cin, c.taps, c.epi);
-        e->kernels[i - 1] = f ? "conv (in " + e->names[i] + ")" : conv_kernel_name(dt, p.variant, p.cin, p.taps, p.epi);
-    }
-}
-
-// Kernel names of the launches a fused transposed conv involves.
-void name_up(pvf_engine* e)
-{
-    const int dt = e->spec.compute_dtype;
-    for (size_t i = 0; i + 1 < e->conv.size(); ++i) {
+        return conv_kernel_name(dt, variant(i), c.cin, c.taps, epi);
+    };
+    std::vector<std::string> k(e->names.size());
+    k[0] = track_kernel_name(dt, e->track_blocks > 0, e->spec.n_bins / e->spec.bins_per_interval,
+                             e->spec.bins_per_interval, n_events);
+    k.back() = "peak_finder";
+    for (size_t i = 1; i + 1 < k.size(); ++i) {
         const auto& c = e->conv[i];
-        if (!c.up) continue;
-        const auto& u = e->conv[i + 1];
-        const bool f = fuses_up(e, (int)i);
-        e->kernels[i] = conv_kernel_name(dt, c.variant, c.cin, c.taps, f ? EPI_UP : c.epi);
-        e->kernels[i + 1] = f ? "transposed conv (in " + e->names[i] + ")"
-                              : conv_kernel_name(dt, u.variant, u.cin, u.taps, u.epi);
+        if (c.variant < 0) {
+            k[i] = "first_conv";
+            continue;
+        }
+        const int v = variant(i);
+        k[i] = conv_name(i, c.epi);
+        // launches that also do a neighbour's work
+        if (fuses_first(e, (int)i, v)) {
+            k[i] = conv_first_kernel_name(dt, v);
+            k[i - 1] = "first_conv (in " + e->names[i] + ")";
+        }
+        if (fuses_pair(e, (int)i, v)) {
+            k[i] = lp_pair_kernel_name(dt);
+            k[i - 1] = "conv (in " + e->names[i] + ")";
+        }
+        if (fuses_dec0(e, (int)i, v)) k[i - 1] = "conv (in " + e->names[i] + ")";
+        if (i > 1 && fuses_up(e, (int)i - 1, variant(i - 1))) {
+            k[i - 1] = conv_name(i - 1, EPI_UP);
+            k[i] = "transposed conv (in " + e->names[i - 1] + ")";
+        }
     }
-}
-
-// Kernel names of enc0.c1 and enc0.c2 for enc0.c2's current variant.
-void name_first(pvf_engine* e)
-{
-    for (size_t i = 1; i < e->conv.size(); ++i) {
-        const auto& c = e->conv[i];
-        if (!c.first) continue;
-        const bool f = conv_first_ok(e->spec.compute_dtype, c.variant);
-        e->kernels[i] = f ? conv_first_kernel_name(e->spec.compute_dtype, c.variant)
-                          : conv_kernel_name(e->spec.compute_dtype, c.variant, c.cin, c.taps, c.epi);
-        e->kernels[i - 1] = f ? "first_conv (in enc0.c2)" : "first_conv";
-    }
+    return k;
 }
 
 void build_names(pvf_engine* e)
@@ -541,7 +529,6 @@ void build_names(pvf_engine* e)
     const int c0 = e->spec.base_channels;
     const WeightLayout& W = e->wl;
     e->names.clear();
-    e->kernels.clear();
     e->conv.clear();
     e->out_channels.clear();
     auto find = [&](const std::string& name) {
@@ -549,15 +536,15 @@ void build_names(pvf_engine* e)
             if (e->names[i] == name) return (int)i;
         return -1;
     };
-    auto plain = [&](const std::string& name, const std::string& kernel, int stored_channels) {
+    auto plain = [&](const std::string& name, int stored_channels) {
         e->names.push_back(name);
-        e->kernels.push_back(kernel);
         e->conv.push_back({});
         e->out_channels.push_back(stored_channels);
     };
-    auto conv = [&](const std::string& name, int gemm_n, int cout, int cin, int taps, Epi epi,
+    auto conv = [&](const std::string& name, int level, int gemm_n, int cout, int cin, int taps, Epi epi,
                     const WeightLayout::Conv* w, std::vector<int> src) {
         pvf_engine::ConvLaunch c;
+        c.level = level;
         c.n = gemm_n;
         c.cout = cout;
         c.cin = cin;
@@ -567,35 +554,32 @@ void build_names(pvf_engine* e)
         c.in_src = std::move(src);
         c.variant = conv_default_variant(e->spec.compute_dtype, gemm_n, cin, taps, epi);
         e->names.push_back(name);
-        e->kernels.push_back(conv_kernel_name(e->spec.compute_dtype, c.variant, cin, taps, epi));
         e->conv.push_back(c);
         e->out_channels.push_back(epi == EPI_HEAD ? 0 : cout);
     };
-    plain("track", track_kernel_name(e->spec.compute_dtype, e->track_blocks > 0,
-                                    e->spec.n_bins / e->spec.bins_per_interval, e->spec.bins_per_interval), 0);
+    plain("track", 0);
     for (int l = 0; l < n; ++l) {
         const std::string L = std::to_string(l);
         const int C = c0 << l;
-        if (l == 0) plain("enc0.c1", "first_conv", C);
-        else conv("enc" + L + ".c1", C, C, C / 2, kTaps, EPI_STORE, &W.enc[l][0],
+        if (l == 0) plain("enc0.c1", C);
+        else conv("enc" + L + ".c1", l, C, C, C / 2, kTaps, EPI_STORE, &W.enc[l][0],
                   {find("enc" + std::to_string(l - 1) + ".c2")});
-        conv("enc" + L + ".c2", C, C, C, kTaps, l < n - 1 ? EPI_POOL : EPI_STORE, &W.enc[l][1],
+        conv("enc" + L + ".c2", l, C, C, C, kTaps, l < n - 1 ? EPI_POOL : EPI_STORE, &W.enc[l][1],
              {find("enc" + L + ".c1")});
     }
     for (int l = n - 2; l >= 0; --l) {
         const std::string L = std::to_string(l);
         const int C = c0 << l;
-        conv("up" + L, 2 * C, C, 2 * C, 1, EPI_CONVT, &W.up[l],
+        conv("up" + L, l + 1, 2 * C, C, 2 * C, 1, EPI_CONVT, &W.up[l],
              {find(l == n - 2 ? "enc" + std::to_string(n - 1) + ".c2" : "dec" + std::to_string(l + 1) + ".c2")});
-        conv("dec" + L + ".c1", C, C, 2 * C, kTaps, EPI_STORE, &W.dec[l][0], {find("enc" + L + ".c2"), find("up" + L)});
-        conv(l == 0 ? "dec0.c2+head" : "dec" + L + ".c2", C, C, C, kTaps, l == 0 ? EPI_HEAD : EPI_STORE,
+        conv("dec" + L + ".c1", l, C, C, 2 * C, kTaps, EPI_STORE, &W.dec[l][0], {find("enc" + L + ".c2"), find("up" + L)});
+        conv(l == 0 ? "dec0.c2+head" : "dec" + L + ".c2", l, C, C, C, kTaps, l == 0 ? EPI_HEAD : EPI_STORE,
              &W.dec[l][1], {find("dec" + L + ".c1")});
     }
-    plain("peaks", "peak_finder", 0);
+    plain("peaks", 0);
     // enc0.c2 (launch 2, after the track stage and enc0.c1) can take the first
     // convolution into its staging when it has the max-pool epilogue
     if (n > 1) e->conv[2].first = true;
-    name_first(e);
     // dec(l+1).c2 feeds only up(l) (l + 1 <= n - 2): it may run it itself, and
     // takes a tile variant that can when there is one
     for (int l = n - 3; l >= 0; --l) {
@@ -606,7 +590,6 @@ void build_names(pvf_engine* e)
         const int v = conv_default_up_variant(e->spec.compute_dtype, c.n, c.cin);
         if (v >= 0) c.variant = v;
     }
-    name_up(e);
     // enc(l).c2 of 64 channels may compute enc(l).c1 (the launch before it) itself
     if (act_bytes(e->spec.compute_dtype) == 2)
         for (int l = 1; l < n - 1; ++l) {
@@ -616,7 +599,6 @@ void build_names(pvf_engine* e)
             c.pair = c.n == 64 && c.cin == 64 && e->conv[p - 1].n == 64;
             if (c.pair) c.variant = lp_default_pair_variant();
         }
-    name_pair(e);
     // dec0.c2 + head may compute dec0.c1 (the launch before it) itself
     {
         const int h = find("dec0.c2+head");
@@ -627,7 +609,7 @@ void build_names(pvf_engine* e)
             if (v >= 0 && conv_variant_ok(e->spec.compute_dtype, v, c.n, c.cin, c.taps, c.epi)) c.variant = v;
         }
     }
-    name_dec0(e);
+    e->kernels = kernel_names(e, 0);
     // calibration table: the stored tensors' channels, in launch order
     e->calib_off.assign(e->names.size(), 0);
     e->calib_total = 0;
@@ -1314,6 +1296,14 @@ const char* pvf_launch_kernel(const pvf_engine* eng, int i)
     return eng->kernels[i].c_str();
 }
 
+const char* pvf_launch_kernel_at(pvf_engine* eng, int i, int32_t n_events)
+{
+    if (!eng || i < 0 || i >= (int)eng->names.size() || n_events < 1 || n_events > eng->spec.max_events) return nullptr;
+    std::vector<std::string> k = kernel_names(eng, n_events);
+    if (k != eng->kernels_at) eng->kernels_at.swap(k);
+    return eng->kernels_at[i].c_str();
+}
+
 int pvf_launch_variant_count(const pvf_engine* eng, int i)
 {
     if (!eng || i < 0 || i >= (int)eng->conv.size() || eng->conv[i].variant < 0) return 0;
@@ -1333,11 +1323,7 @@ pvf_status pvf_set_launch_variant(pvf_engine* eng, int i, int v)
     if (!conv_variant_ok(eng->spec.compute_dtype, v, c.n, c.cin, c.taps, c.epi)) return PVF_ERR_INVALID_ARGUMENT;
     c.variant = v;
     c.pinned = true;
-    eng->kernels[i] = conv_kernel_name(eng->spec.compute_dtype, v, c.cin, c.taps, c.epi);
-    name_first(eng);
-    name_up(eng);
-    name_pair(eng);
-    name_dec0(eng);
+    eng->kernels = kernel_names(eng, 0);
     return PVF_OK;
 }
 
@@ -1398,7 +1384,7 @@ pvf_status pvf_set_track_schedule(pvf_engine* eng, int persistent)
     const int n_out = eng->spec.bins_per_interval;
     eng->track_blocks =
         persistent ? track_queue_blocks(eng->spec.compute_dtype, n_intervals, n_out, eng->cu_count) : 0;
-    eng->kernels[0] = track_kernel_name(eng->spec.compute_dtype, persistent, n_intervals, n_out);
+    eng->kernels = kernel_names(eng, 0);
     return PVF_OK;
 }
 

@@ -261,8 +261,8 @@ hipError_t launch_track(const TrackArgs& a, int n_events, int persistent_blocks,
 // Blocks of the track stage's work-queue form for this engine: as many as fit
 // on the device at once.
 int track_queue_blocks(int dtype, int n_intervals, int n_out, int cu_count);
-// Name of the track-stage kernel an engine launches.
-std::string track_kernel_name(int dtype, bool persistent, int n_intervals, int n_out);
+// Name of the track-stage kernel an engine launches for n_events (0: a full batch).
+std::string track_kernel_name(int dtype, bool persistent, int n_intervals, int n_out, int n_events);
 hipError_t launch_first_conv(const FirstConvArgs& a, int dtype, hipStream_t s);
 // Conv launches run one of several tile-shape variants of the kernel for
 // the compute dtype; all variants of a dtype give identical bits.

@@ -1278,10 +1278,11 @@ int track_queue_blocks(int dtype, int n_intervals, int n_out, int cu_count)
     return (err == hipSuccess && per_cu > 0 ? per_cu : 1) * cu_count;
 }
 
-std::string track_kernel_name(int dtype, bool persistent, int n_intervals, int n_out)
+std::string track_kernel_name(int dtype, bool persistent, int n_intervals, int n_out, int n_events)
 {
     static const char* const kType[] = {"float", "__bf16", "_Float16", "unsigned char"};
-    if (track_mma_ok(n_intervals, n_out)) return std::string("track_stage_mma<") + kType[dtype] + ", 4>";
+    if (track_mma_ok(n_intervals, n_out))
+        return std::string("track_stage_mma<") + kType[dtype] + (n_events > 0 && n_events <= kWideEvents ? ", 8>" : ", 4>");
     return std::string(persistent ? "track_stage_queue<" : "track_stage<") + kType[dtype] + ">";
 }
 
