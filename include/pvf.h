@@ -246,8 +246,9 @@ const char *pvf_status_string(pvf_status s);
  * histograms of up to 48 intervals, two for longer ones) takes them from a
  * device work queue, so heavy-tailed batches do not end on their largest
  * events; with up to 48 intervals the queue is skipped, and each event has a
- * block (two in batches of up to 128 events), when the batch fits on the device
- * at once.  persistent = 0: no queue for any batch.  Results are identical either way. */
+ * block (two in batches of at most one event to two compute units), when the
+ * batch fits on the device at once.  persistent = 0: no queue for any batch.
+ * Results are identical either way. */
 pvf_status pvf_set_track_schedule(pvf_engine *eng, int persistent);
 
 /* Capture the whole path for this batch view (its pointers and counts are

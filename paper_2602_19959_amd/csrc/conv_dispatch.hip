@@ -53,11 +53,11 @@ int conv_default_variant(int dtype, int n, int cin, int taps, Epi epi)
     return lp_default_variant(n, cin, taps, epi);
 }
 
-int conv_batch_variant(int dtype, int full, int n, int cin, Epi epi, int m_rows)
+int conv_batch_variant(int dtype, int full, int n, int cin, Epi epi, int m_rows, int cus)
 {
-    if (dtype == PVF_FP32) return f32_batch_variant(full, n, epi, m_rows);
-    if (dtype == PVF_FP8_E4M3) return fp8_batch_variant(full, n, cin, epi, m_rows);
-    return lp_batch_variant(full, n, cin, epi, m_rows);
+    if (dtype == PVF_FP32) return f32_batch_variant(full, n, epi, m_rows, cus);
+    if (dtype == PVF_FP8_E4M3) return fp8_batch_variant(full, n, cin, epi, m_rows, cus);
+    return lp_batch_variant(full, n, cin, epi, m_rows, cus);
 }
 
 int conv_default_up_variant(int dtype, int n, int cin)

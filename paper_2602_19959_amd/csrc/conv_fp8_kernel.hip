@@ -882,13 +882,12 @@ int fp8_default_variant(int n, int cin, int taps, Epi epi)
 // 256 x 32, 15.0; 100 events 24.6, 25.4; 200 events 40.4, 38.9).  The fused
 // launches keep their tiles (dec2.c2 with up1, one event: 6.9 us, apart 5.9 and
 // a launch more).
-int fp8_batch_variant(int full, int n, int cin, Epi epi, int m_rows)
+int fp8_batch_variant(int full, int n, int cin, Epi epi, int m_rows, int cus)
 {
-    constexpr int kCus = 256;
     if (epi == EPI_UP || epi == EPI_HEAD || fp8_first_ok(full)) return full;
     int v = full;
-    if (tile_blocks(m_rows, n, 64, 32) <= 3 * kCus) v = cin % 64 == 0 ? 23 : 24;
-    else if (epi != EPI_CONVT && tile_blocks(m_rows, n, 256, 32) <= (cin % 64 == 0 ? 8 : 4) * kCus) v = cin % 64 == 0 ? 15 : 18;
+    if (tile_blocks(m_rows, n, 64, 32) <= 3 * cus) v = cin % 64 == 0 ? 23 : 24;
+    else if (epi != EPI_CONVT && tile_blocks(m_rows, n, 256, 32) <= (cin % 64 == 0 ? 8 : 4) * cus) v = cin % 64 == 0 ? 15 : 18;
     return fp8_variant_ok(v, n, cin, epi == EPI_CONVT ? 1 : kTaps, epi) ? v : full;
 }
 

@@ -618,14 +618,14 @@ int f32_default_variant(int n, int cin, int taps, Epi epi)
 // 32 x 32 tiles 12 us, 64 x 32 14 us, 128 x 32 23 us, 128 x 128 42 us; eight
 // events, 1008 32 x 32 blocks: 27 us against 19 us with 64 x 32; 16 events, 1008
 // 64 x 32 blocks: 36 us against 31 us with 128 x 32).
-int f32_batch_variant(int full, int n, Epi epi, int m_rows)
+int f32_batch_variant(int full, int n, Epi epi, int m_rows, int cus)
 {
-    constexpr int kAtOnce = 3 * 256;
-    if (epi == EPI_HEAD && n == 64) return tile_blocks(m_rows, n, 64, 64) <= kAtOnce ? 18 : full;
-    if (tile_blocks(m_rows, n, 32, 32) <= kAtOnce) return 16;
-    if (tile_blocks(m_rows, n, 64, 32) <= kAtOnce) return 15;
-    if (tile_blocks(m_rows, n, 128, 32) <= kAtOnce) return 17;
-    if (n >= 64 && tile_blocks(m_rows, n, 128, 64) <= kAtOnce) return 4;
+    const int at_once = 3 * cus;
+    if (epi == EPI_HEAD && n == 64) return tile_blocks(m_rows, n, 64, 64) <= at_once ? 18 : full;
+    if (tile_blocks(m_rows, n, 32, 32) <= at_once) return 16;
+    if (tile_blocks(m_rows, n, 64, 32) <= at_once) return 15;
+    if (tile_blocks(m_rows, n, 128, 32) <= at_once) return 17;
+    if (n >= 64 && tile_blocks(m_rows, n, 128, 64) <= at_once) return 4;
     return full;
 }
 

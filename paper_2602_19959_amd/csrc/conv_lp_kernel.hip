@@ -1570,43 +1570,42 @@ int lp_default_up_variant(int n, int cin)
 // 32 x 32 tiles, 8.8 with 64 x 32, 11.4 with 128 x 32, 17.4 with the default
 // 256 x 64; 16 events 14.1 with 64 x 32 and 20.3; 32 events 16.8 with 256 x 32
 // and 22.7; 48 events 22.1 and 24.4; 64 events 27.8 and 26.1, so the default.
-int lp_batch_variant(int full, int n, int cin, Epi epi, int m_rows)
+int lp_batch_variant(int full, int n, int cin, Epi epi, int m_rows, int cus)
 {
-    constexpr int kCus = 256;
     if (lp_pair_ok(full)) {
         // enc1.c2 with enc1.c1: three blocks of 240 rows to a compute unit, so
-        // rounds of 768 blocks, taken when there are more than two or three quarters
+        // rounds of 768 blocks on 256 of them, taken when there are more than two or three quarters
         // of the slots of one or two are filled.  Both launches' time, fused and apart: 48
         // events (0.5 rounds) 17 us and 14; 90 (0.98) 22 and 27; 97 (1.05) 31
         // and 27; 128 (1.4) 35 and 33; 160 (1.7) 37 and 44; 250 (2.7) 53 and 64
-        const int64_t blocks = tile_blocks(m_rows, n, 240, 64), round = 3 * kCus;
+        const int64_t blocks = tile_blocks(m_rows, n, 240, 64), round = 3 * cus;
         if (blocks > 2 * round || 4 * blocks >= 3 * round * ((blocks + round - 1) / round)) return full;
         full = 28;
     }
     int v = full;
     if (lp_dec0_ok(full)) {
         // dec0.c1 and the head in one launch: 240 rows a block while that fills at most one round (one event 7.8 us, 8.6 with 496)
-        return tile_blocks(m_rows, n, 240, 32) <= kCus ? 31 : full;
+        return tile_blocks(m_rows, n, 240, 32) <= cus ? 31 : full;
     } else if (kVariants[full].pf == 6) {
         // enc0.c2 with the first convolution: blocks of 128, 256 or 512 rows
-        v = tile_blocks(m_rows, n, 128, 32) <= kCus ? 33 : tile_blocks(m_rows, n, 256, 32) <= kCus ? 34 : full;
+        v = tile_blocks(m_rows, n, 128, 32) <= cus ? 33 : tile_blocks(m_rows, n, 256, 32) <= cus ? 34 : full;
     } else if (epi == EPI_UP && n == 64) {
         // with the transposed conv in the epilogue, all columns in a block: 32,
         // 64 or 128 rows (one event 2.7 us, 10 with 512 x 64; 32 events 9.2 and 12.4)
-        if (tile_blocks(m_rows, n, 32, 64) <= kCus) v = 40;
-        else if (tile_blocks(m_rows, n, 64, 64) <= 2 * kCus) v = 41;
-        else if (tile_blocks(m_rows, n, 128, 64) <= 2 * kCus) v = 4;
+        if (tile_blocks(m_rows, n, 32, 64) <= cus) v = 40;
+        else if (tile_blocks(m_rows, n, 64, 64) <= 2 * cus) v = 41;
+        else if (tile_blocks(m_rows, n, 128, 64) <= 2 * cus) v = 4;
     } else if (epi == EPI_UP && n == 128) {
         // the same: one event 5.4 us, 16 with the default 256 x 128; 32 events 13.8 and 19
-        if (tile_blocks(m_rows, n, 32, 128) <= kCus) v = 38;
-        else if (tile_blocks(m_rows, n, 64, 128) <= kCus) v = 39;
-        else if (tile_blocks(m_rows, n, 128, 128) <= kCus) v = 15;
+        if (tile_blocks(m_rows, n, 32, 128) <= cus) v = 38;
+        else if (tile_blocks(m_rows, n, 64, 128) <= cus) v = 39;
+        else if (tile_blocks(m_rows, n, 128, 128) <= cus) v = 15;
     } else if (epi != EPI_HEAD || n == 32) {
-        if (tile_blocks(m_rows, n, 32, 32) <= 3 * kCus) v = 37;
-        else if (tile_blocks(m_rows, n, 64, 32) <= 4 * kCus) v = 36;
+        if (tile_blocks(m_rows, n, 32, 32) <= 3 * cus) v = 37;
+        else if (tile_blocks(m_rows, n, 64, 32) <= 4 * cus) v = 36;
         else if (epi == EPI_CONVT) v = full;
-        else if (tile_blocks(m_rows, n, 256, 32) <= 2 * kCus) v = 14;
-        else if (tile_blocks(m_rows, n, 256, 32) <= 3 * kCus && n > 32) v = cin % 64 == 0 ? 8 : 29;
+        else if (tile_blocks(m_rows, n, 256, 32) <= 2 * cus) v = 14;
+        else if (tile_blocks(m_rows, n, 256, 32) <= 3 * cus && n > 32) v = cin % 64 == 0 ? 8 : 29;
     }
     return lp_variant_ok(v, n, cin, epi == EPI_CONVT ? 1 : kTaps, epi) ? v : full;
 }

@@ -210,18 +210,16 @@ __global__ __launch_bounds__(NT) void peak_finder(PeakArgs a)
     }
 }
 
-// One block a compute unit: 1024 threads (one event 7 us, 10.5 with 256; 200
-// events 10 and 14; 300 events 17 either way).
-constexpr int kWideEvents = 256;
-
 }  // namespace
 
-hipError_t launch_peaks(const PeakArgs& a, int n_events, hipStream_t s)
+hipError_t launch_peaks(const PeakArgs& a, int n_events, int cus, hipStream_t s)
 {
     // strict local maxima are never adjacent: at most L / 2 candidates
     if (a.L < 3 || a.L > kMaxBins || a.hw < 0) return hipErrorInvalidValue;
     const size_t lds = sizeof(float) * a.L + sizeof(uint16_t) * (a.L / 2 + 1);
-    const bool wide = n_events <= kWideEvents;
+    // at most one block a compute unit: 1024 threads (one event 7 us, 10.5 with
+    // 256; 200 events 10 and 14; 300 events, on 256 units, 17 either way)
+    const bool wide = n_events <= cus;
     if (a.hw == 5) {
         if (wide) hipLaunchKernelGGL((peak_finder<5, 1024>), dim3(n_events), dim3(1024), lds, s, a);
         else hipLaunchKernelGGL((peak_finder<5, 256>), dim3(n_events), dim3(256), lds, s, a);

@@ -439,7 +439,7 @@ int tile(const pvf_engine* e, int i, int m_rows)
     if (c.variant < 0 || c.pinned) return c.variant;
     const int dt = e->spec.compute_dtype;
     const bool up = c.up && dt != PVF_FP32 && conv_variant_ok(dt, c.variant, c.n, c.cin, c.taps, EPI_UP);
-    return conv_batch_variant(dt, c.variant, c.n, c.cin, up ? EPI_UP : c.epi, m_rows);
+    return conv_batch_variant(dt, c.variant, c.n, c.cin, up ? EPI_UP : c.epi, m_rows, e->cu_count);
 }
 
 // Whether launch i (enc0.c2) with tile variant v computes the first
@@ -495,7 +495,7 @@ std::vector<std::string> kernel_names(const pvf_engine* e, int n_events)
     };
     std::vector<std::string> k(e->names.size());
     k[0] = track_kernel_name(dt, e->track_blocks > 0, e->spec.n_bins / e->spec.bins_per_interval,
-                             e->spec.bins_per_interval, n_events);
+                             e->spec.bins_per_interval, n_events, e->cu_count);
     k.back() = "peak_finder";
     for (size_t i = 1; i + 1 < k.size(); ++i) {
         const auto& c = e->conv[i];
@@ -840,7 +840,7 @@ pvf_status enqueue(pvf_engine* eng, const pvf_tracks* tr, const pvf_vertices* ou
     ta.flags = flags;
     ta.order = reinterpret_cast<int32_t*>(wk(P.order));
     ta.queue_counter = reinterpret_cast<int32_t*>(wk(P.queue));
-    check(launch_track(ta, E, eng->track_blocks, s));
+    check(launch_track(ta, E, eng->track_blocks, eng->cu_count, s));
 
     // Calibration (pvf_calibrate only): per-channel absolute maximum of the
     // tensor the launch just enqueued stored.
@@ -1018,7 +1018,7 @@ pvf_status enqueue(pvf_engine* eng, const pvf_tracks* tr, const pvf_vertices* ou
     pa.integral = out->d_integral;
     pa.status = out->d_event_status;
     pa.bin = out->d_bin;
-    check(launch_peaks(pa, E, s));
+    check(launch_peaks(pa, E, eng->cu_count, s));
     return err == hipSuccess ? PVF_OK : PVF_ERR_DEVICE;
 }
 

@@ -257,12 +257,12 @@ hipError_t launch_amax(const AmaxArgs& a, hipStream_t s);
 
 // persistent_blocks > 0: the work-queue form (order kernel + persistent
 // blocks, a.order and a.queue_counter set).  Otherwise one block per event.
-hipError_t launch_track(const TrackArgs& a, int n_events, int persistent_blocks, hipStream_t s);
+hipError_t launch_track(const TrackArgs& a, int n_events, int persistent_blocks, int cus, hipStream_t s);
 // Blocks of the track stage's work-queue form for this engine: as many as fit
 // on the device at once.
 int track_queue_blocks(int dtype, int n_intervals, int n_out, int cu_count);
 // Name of the track-stage kernel an engine launches for n_events (0: a full batch).
-std::string track_kernel_name(int dtype, bool persistent, int n_intervals, int n_out, int n_events);
+std::string track_kernel_name(int dtype, bool persistent, int n_intervals, int n_out, int n_events, int cus);
 hipError_t launch_first_conv(const FirstConvArgs& a, int dtype, hipStream_t s);
 // Conv launches run one of several tile-shape variants of the kernel for
 // the compute dtype; all variants of a dtype give identical bits.
@@ -278,11 +278,11 @@ std::string conv_first_kernel_name(int dtype, int variant);
 int conv_variant_count(int dtype);
 bool conv_variant_ok(int dtype, int variant, int n, int cin, int taps, Epi epi);
 int conv_default_variant(int dtype, int n, int cin, int taps, Epi epi);
-// Variant to run in place of the default `full` for a batch of m_rows rows:
-// a smaller tile while the default's would leave compute units idle.  epi:
+// Variant to run in place of the default `full` for a batch of m_rows rows on
+// a device of `cus` compute units: a smaller tile while the default's would leave compute units idle.  epi:
 // EPI_UP where the default runs the next transposed conv in its epilogue (as
 // the variant returned does then).
-int conv_batch_variant(int dtype, int full, int n, int cin, Epi epi, int m_rows);
+int conv_batch_variant(int dtype, int full, int n, int cin, Epi epi, int m_rows, int cus);
 // Blocks of a bm x bn tiling of m_rows x n outputs
 inline int64_t tile_blocks(int m_rows, int n, int bm, int bn) { return ((int64_t)m_rows + bm - 1) / bm * ((n + bn - 1) / bn); }
 // Default tile variant of a 5-tap launch that runs the transposed conv after
@@ -304,7 +304,7 @@ float f32_split_cut(float w_sum);
 int f32_variant_count();
 bool f32_variant_ok(int variant, int n, int taps, Epi epi);
 int f32_default_variant(int n, int cin, int taps, Epi epi);
-int f32_batch_variant(int full, int n, Epi epi, int m_rows);
+int f32_batch_variant(int full, int n, Epi epi, int m_rows, int cus);
 std::string f32_kernel_name(int variant, int taps, Epi epi);
 hipError_t launch_conv_f32_first(const ConvArgs& a, int variant, hipStream_t s);
 bool f32_first_ok(int variant);
@@ -313,7 +313,7 @@ hipError_t launch_conv_lp(int dtype, const ConvArgs& a, int taps, Epi epi, int v
 int lp_variant_count();
 bool lp_variant_ok(int variant, int n, int cin, int taps, Epi epi);
 int lp_default_variant(int n, int cin, int taps, Epi epi);
-int lp_batch_variant(int full, int n, int cin, Epi epi, int m_rows);
+int lp_batch_variant(int full, int n, int cin, Epi epi, int m_rows, int cus);
 std::string lp_kernel_name(int dtype, int variant, int taps, Epi epi);
 hipError_t launch_conv_lp_first(int dtype, const ConvArgs& a, int variant, hipStream_t s);
 bool lp_first_ok(int variant);
@@ -345,12 +345,12 @@ hipError_t launch_conv_fp8(const ConvArgs& a, int taps, Epi epi, int variant, hi
 int fp8_variant_count();
 bool fp8_variant_ok(int variant, int n, int cin, int taps, Epi epi);
 int fp8_default_variant(int n, int cin, int taps, Epi epi);
-int fp8_batch_variant(int full, int n, int cin, Epi epi, int m_rows);
+int fp8_batch_variant(int full, int n, int cin, Epi epi, int m_rows, int cus);
 std::string fp8_kernel_name(int variant, int cin, int taps, Epi epi);
 
 inline int act_bytes(int dtype) { return dtype == PVF_FP32 ? 4 : (dtype == PVF_FP8_E4M3 ? 1 : 2); }
 
-hipError_t launch_peaks(const PeakArgs& a, int n_events, hipStream_t s);
+hipError_t launch_peaks(const PeakArgs& a, int n_events, int cus, hipStream_t s);
 
 // The library's fixed per-device scratch areas (pvf_execute_scratch).
 constexpr size_t kScratchBytes = PVF_SCRATCH_BYTES;

@@ -1185,15 +1185,23 @@ static size_t track_mma_lds_bytes()
     return row_tile_bytes<E>() + 3 * NT * sizeof(int);
 }
 
-// Batches that leave compute units idle: up to 384 events eight waves an event,
-// up to 128 two blocks of them.  One event 36.5 us with the four-wave form in
-// FP32, 27 with eight waves, 21 with two blocks of eight (BF16 18, 15, 13); 333
-// heavy-tailed FP32 events (the largest of 1500 tracks) 253 and 193; at 500
-// FP32 events the four-wave form's 64 us beat 70.
-constexpr int kWideEvents = 384, kSplitEvents = 128;
+// Batches that leave compute units idle: up to three events to two compute
+// units eight waves an event, up to one to two units two blocks of them.
+// Track stage, us, four waves / eight / two blocks of eight, Poisson counts and
+// (heavy-tailed ones), 256 units:
+//              FP32                               BF16
+//   1 event    45 / 34 / 27   (197 / 150 / 117)   21 / 16 / 17   (72 / 66 / 54)
+//   128        48 / 39 / 32   (236 / 183 / 141)   25 / 23 / 22   (91 / 81 / 65)
+//   256        50 / 40 / 58   (247 / 187 / 177)   27 / 24 / 26   (92 / 81 / 72)
+//   384        66 / 71 / 84   (265 / 222 / 226)   33 / 29 / 36   (95 / 88 / 83)
+//   512        70 / 76 / 111  (302 / 246 / 269)   30 / 30 / 40   (113 / 109 / 106)
+// FP16 as BF16; FP8 at 128, 256 and 384 events 27 / 23 / 22 (102 / 87 / 74), 30 /
+// 25 / 37 (107 / 90 / 96), 35 / 39 / 47 (109 / 106 / 119).
+static bool track_wide(int n_events, int cus) { return 2 * (int64_t)n_events <= 3 * (int64_t)cus; }
+static bool track_split(int n_events, int cus) { return 2 * (int64_t)n_events <= cus; }
 
 template <class E>
-hipError_t launch_track_typed(const TrackArgs& a, int n_events, int persistent_blocks, hipStream_t s)
+hipError_t launch_track_typed(const TrackArgs& a, int n_events, int persistent_blocks, int cus, hipStream_t s)
 {
     if (a.n_out < 1 || a.n_out > NT) return hipErrorInvalidValue;   // one thread per output column
     {
@@ -1206,8 +1214,8 @@ hipError_t launch_track_typed(const TrackArgs& a, int n_events, int persistent_b
                 const hipError_t err = hipGetLastError();
                 if (err != hipSuccess) return err;
             }
-            const int split = n_events <= kSplitEvents;
-            if (!a.mlp_calib && n_events <= kWideEvents)
+            const int split = track_split(n_events, cus);
+            if (!a.mlp_calib && track_wide(n_events, cus))
                 hipLaunchKernelGGL((track_stage_mma<E, 8>), dim3(n_events * (1 + split)), dim3(512), track_mma_lds_bytes<E>(), s, a,
                                    n_events, 0, split);
             else
@@ -1237,16 +1245,16 @@ hipError_t launch_track_typed(const TrackArgs& a, int n_events, int persistent_b
     return hipGetLastError();
 }
 
-hipError_t launch_track(const TrackArgs& a, int n_events, int persistent_blocks, hipStream_t s)
+hipError_t launch_track(const TrackArgs& a, int n_events, int persistent_blocks, int cus, hipStream_t s)
 {
     if (a.mlp_dtype != PVF_FP32 && (!a.mlp_lp || a.n_out > kMlpOutN ||
                                     (a.mlp_dtype == PVF_FP8_E4M3 && (!a.mlp_in_inv || !a.mlp_col))))
         return hipErrorInvalidValue;
     switch (a.mlp_dtype) {
-    case PVF_FP32: return launch_track_typed<float>(a, n_events, persistent_blocks, s);
-    case PVF_BF16: return launch_track_typed<__bf16>(a, n_events, persistent_blocks, s);
-    case PVF_FP16: return launch_track_typed<_Float16>(a, n_events, persistent_blocks, s);
-    case PVF_FP8_E4M3: return launch_track_typed<uint8_t>(a, n_events, persistent_blocks, s);
+    case PVF_FP32: return launch_track_typed<float>(a, n_events, persistent_blocks, cus, s);
+    case PVF_BF16: return launch_track_typed<__bf16>(a, n_events, persistent_blocks, cus, s);
+    case PVF_FP16: return launch_track_typed<_Float16>(a, n_events, persistent_blocks, cus, s);
+    case PVF_FP8_E4M3: return launch_track_typed<uint8_t>(a, n_events, persistent_blocks, cus, s);
     default: return hipErrorInvalidValue;
     }
 }
@@ -1278,11 +1286,11 @@ int track_queue_blocks(int dtype, int n_intervals, int n_out, int cu_count)
     return (err == hipSuccess && per_cu > 0 ? per_cu : 1) * cu_count;
 }
 
-std::string track_kernel_name(int dtype, bool persistent, int n_intervals, int n_out, int n_events)
+std::string track_kernel_name(int dtype, bool persistent, int n_intervals, int n_out, int n_events, int cus)
 {
     static const char* const kType[] = {"float", "__bf16", "_Float16", "unsigned char"};
     if (track_mma_ok(n_intervals, n_out))
-        return std::string("track_stage_mma<") + kType[dtype] + (n_events > 0 && n_events <= kWideEvents ? ", 8>" : ", 4>");
+        return std::string("track_stage_mma<") + kType[dtype] + (n_events > 0 && track_wide(n_events, cus) ? ", 8>" : ", 4>");
     return std::string(persistent ? "track_stage_queue<" : "track_stage<") + kType[dtype] + ">";
 }
 
