@@ -1186,7 +1186,8 @@ static size_t track_mma_lds_bytes()
 }
 
 // Batches that leave compute units idle: up to three events to two compute
-// units eight waves an event, up to one to two units two blocks of them.
+// units (FP8: one to one) eight waves an event, up to one to two units two
+// blocks of them.
 // Track stage, us, four waves / eight / two blocks of eight, Poisson counts and
 // (heavy-tailed ones), 256 units:
 //              FP32                               BF16
@@ -1195,9 +1196,14 @@ static size_t track_mma_lds_bytes()
 //   256        50 / 40 / 58   (247 / 187 / 177)   27 / 24 / 26   (92 / 81 / 72)
 //   384        66 / 71 / 84   (265 / 222 / 226)   33 / 29 / 36   (95 / 88 / 83)
 //   512        70 / 76 / 111  (302 / 246 / 269)   30 / 30 / 40   (113 / 109 / 106)
-// FP16 as BF16; FP8 at 128, 256 and 384 events 27 / 23 / 22 (102 / 87 / 74), 30 /
-// 25 / 37 (107 / 90 / 96), 35 / 39 / 47 (109 / 106 / 119).
-static bool track_wide(int n_events, int cus) { return 2 * (int64_t)n_events <= 3 * (int64_t)cus; }
+// FP16 as BF16; FP8 at 128, 256, 320 and 384 events 27 / 23 / 22 (102 / 87 / 74),
+// 30 / 25 / 37 (107 / 90 / 96), 36 / 40 / 48 (111 / 99 / 108), 35 / 39 / 47 (109
+// / 106 / 119): past one event to a unit it loses on even batches 12 % of the
+// stage, 1 % of the call.
+static bool track_wide(int dtype, int n_events, int cus)
+{
+    return dtype == PVF_FP8_E4M3 ? n_events <= cus : 2 * (int64_t)n_events <= 3 * (int64_t)cus;
+}
 static bool track_split(int n_events, int cus) { return 2 * (int64_t)n_events <= cus; }
 
 template <class E>
@@ -1215,7 +1221,7 @@ hipError_t launch_track_typed(const TrackArgs& a, int n_events, int persistent_b
                 if (err != hipSuccess) return err;
             }
             const int split = track_split(n_events, cus);
-            if (!a.mlp_calib && track_wide(n_events, cus))
+            if (!a.mlp_calib && track_wide(a.mlp_dtype, n_events, cus))
                 hipLaunchKernelGGL((track_stage_mma<E, 8>), dim3(n_events * (1 + split)), dim3(512), track_mma_lds_bytes<E>(), s, a,
                                    n_events, 0, split);
             else
@@ -1290,7 +1296,7 @@ std::string track_kernel_name(int dtype, bool persistent, int n_intervals, int n
 {
     static const char* const kType[] = {"float", "__bf16", "_Float16", "unsigned char"};
     if (track_mma_ok(n_intervals, n_out))
-        return std::string("track_stage_mma<") + kType[dtype] + (n_events > 0 && track_wide(n_events, cus) ? ", 8>" : ", 4>");
+        return std::string("track_stage_mma<") + kType[dtype] + (n_events > 0 && track_wide(dtype, n_events, cus) ? ", 8>" : ", 4>");
     return std::string(persistent ? "track_stage_queue<" : "track_stage<") + kType[dtype] + ">";
 }
 

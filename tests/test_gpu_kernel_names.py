@@ -54,3 +54,16 @@ def test_reported_kernels_are_the_launched_ones(dtype, sizes):
     with pytest.raises(ValueError):
         eng.launch_kernels(max(sizes) + 1)
     eng.close()
+
+
+@pytest.mark.parametrize("dtype", ["fp32", "bf16", "fp16", "fp8_e4m3"])
+def test_track_form_by_batch_size(dtype):
+    """The eight-wave track stage up to one event to a compute unit in FP8 (even
+    batches past that are faster in the four-wave form) and three to two else."""
+    torch = torch_cuda()
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    last = cus if dtype == "fp8_e4m3" else 3 * cus // 2
+    eng = engine_for(last + 1, dtype)
+    for n, waves in ((1, 8), (last, 8), (last + 1, 4)):
+        assert eng.launch_kernels(n)[0].endswith(f", {waves}>"), n
+    eng.close()
