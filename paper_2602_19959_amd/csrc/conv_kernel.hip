@@ -601,7 +601,7 @@ bool f32_variant_ok(int v, int n, int taps, Epi epi)
 // of the 64-channel one): the waves of 32 positions win, as their blocks take
 // half the registers and a third more waves share a CU; 128 columns where
 // there are as many, since a halo tile is then split for twice the columns
-// (enc2.c2 722 us, against 731 with 64 x 64 waves and 724 with 64 columns).
+// (enc3.c2 1393 us, against 1468 with 64 x 64 waves and 1437 with 64 columns).
 int f32_default_variant(int n, int cin, int taps, Epi epi)
 {
     (void)cin;
@@ -614,10 +614,10 @@ int f32_default_variant(int n, int cin, int taps, Epi epi)
 // Tiles of small batches, from sweeps of 1 to 200 events of the 32-channel
 // network.  A launch then waits on one block's serial chain of steps, not on
 // throughput, so the smallest tile wins that still keeps every block on the
-// device at once: three blocks a CU of the deep-ring tiles (enc3.c2, one event:
-// 32 x 32 tiles 12 us, 64 x 32 14 us, 128 x 32 23 us, 128 x 128 42 us; eight
-// events, 1008 32 x 32 blocks: 27 us against 19 us with 64 x 32; 16 events, 1008
-// 64 x 32 blocks: 36 us against 31 us with 128 x 32).
+// device at once: three blocks a CU of the deep-ring tiles (enc3.c2, launch and
+// its event, one event: 32 x 32 tiles 17 us, 64 x 32 20 us, 128 x 32 26 us, 128 x
+// 128 50 us; eight events, 1008 32 x 32 blocks: 33 us against 24 us with 64 x 32;
+// 16 events, 1008 64 x 32 blocks: 41 us against 35 us with 128 x 32).
 int f32_batch_variant(int full, int n, Epi epi, int m_rows, int cus)
 {
     const int at_once = 3 * cus;
