@@ -298,6 +298,9 @@ __device__ __forceinline__ void conv_f32_tile(const ConvArgs& a)
     const char* wt = static_cast<const char*>(a.w) + (int64_t)n0 / 16 * kF32Pieces * FRAG;
     const int64_t wstep = (int64_t)a.n / 16 * kF32Pieces * FRAG;    // bytes of one (chunk, tap) step, all columns
 
+    // column tiles at a time: 2 x 4-tile waves have registers for one at four
+    // waves a SIMD (12 spilled with two, 130 MB of HBM writes a launch at 1000 events)
+    constexpr int JG = TMW * TNW == 8 && TNW == 4 ? 1 : 2;
     f32x4 acc[TMW][TNW];
 #pragma unroll
     for (int i = 0; i < TMW; ++i)
@@ -415,20 +418,20 @@ __device__ __forceinline__ void conv_f32_tile(const ConvArgs& a)
                 for (int i = 0; i < TMW; ++i)
                     xf[i][q] = *reinterpret_cast<const bf16x8*>(xs + q * 4 * PLANE + (i * 16 + tap) * 16);
 #pragma unroll
-            for (int j0 = 0; j0 < TNW; j0 += 2) {
-                bf16x8 wf[2][kF32Pieces];
+            for (int j0 = 0; j0 < TNW; j0 += JG) {
+                bf16x8 wf[JG][kF32Pieces];
 #pragma unroll
                 for (int q = 0; q < kF32Pieces; ++q)
 #pragma unroll
-                    for (int j = 0; j < 2; ++j)
+                    for (int j = 0; j < JG; ++j)
                         wf[j][q] = *reinterpret_cast<const bf16x8*>(ws + ((j0 + j) * kF32Pieces + q) * FRAG);
-                f32x4 low[TMW][2];                 // the step's five smaller products
+                f32x4 low[TMW][JG];                 // the step's five smaller products
 #pragma unroll
                 for (int t = 0; t < kF32Products; ++t)
 #pragma unroll
                     for (int i = 0; i < TMW; ++i)
 #pragma unroll
-                        for (int j = 0; j < 2; ++j) {
+                        for (int j = 0; j < JG; ++j) {
                             f32x4& d = t + 1 < kF32Products ? low[i][j] : acc[i][j0 + j];
                             d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[j][kProd[t][0]], xf[i][kProd[t][1]],
                                                                         t == 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : d, 0, 0, 0);
@@ -436,7 +439,7 @@ __device__ __forceinline__ void conv_f32_tile(const ConvArgs& a)
 #pragma unroll
                 for (int i = 0; i < TMW; ++i)
 #pragma unroll
-                    for (int j = 0; j < 2; ++j)
+                    for (int j = 0; j < JG; ++j)
 #pragma unroll
                         for (int v = 0; v < 4; ++v) acc[i][j0 + j][v] += low[i][j][v];
             }
