@@ -231,8 +231,9 @@ pvf_status pvf_execute_scratch(pvf_engine *eng, const pvf_tracks *tracks, const 
 
 /* Release the engine's host state.  The arena is the caller's to free.  An
  * engine that has made scratch calls first waits for its stream's work (unless
- * the stream is being captured), as its scratch area may go to another engine;
- * graphs of the caller's own that hold its scratch calls must have ended. */
+ * the stream is being captured; the stream must still be there), as its scratch
+ * area may go to another engine; graphs of the caller's own that hold its scratch
+ * calls must have ended. */
 pvf_status pvf_destroy(pvf_engine *eng);
 
 /* Static English text of a status code. */

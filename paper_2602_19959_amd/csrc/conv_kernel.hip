@@ -83,7 +83,9 @@ constexpr int kProd[kF32Products][2] = {{0, 2}, {1, 1}, {2, 0}, {0, 1}, {1, 0}, 
 // |weight| over an output channel (f32_split_cut).  Weights are rounded where
 // that sum is at most kRoundSum: their smaller pieces' products are below 2^-8
 // of theirs, so they stay below 2^127 over finite rows; else they are cut off
-// too.  (Sums within 2^-7 of FP32's largest value may round up to infinity.)
+// too.  (Sums within 2^-7 of FP32's largest value may round up to infinity.
+// Products left out reach 2^-22 with one operand cut off, 2^-21 with both; the
+// measured error of p with every weight cut off is that of rounded ones, 0.42.)
 constexpr float kBf16Cut = 0x1.ffp127f;
 constexpr float kRoundSum = 0x1p7f;
 
